@@ -105,12 +105,13 @@ size_t ts_ffn_workspace_bytes(int batch, int hidden, int inter, ts_dtype wdtype)
  *   out [batch][hidden] fp32; stats nullable; ws/ws_bytes workspace;
  *   stream hipStream_t or NULL.
  * batch == 1 uses the pipelined single-token kernel.  batch > 1 with
- * TS_BF16 weights reads every weight row at most once per pass of up to 64
- * tokens (the rows of the union of the pass's active sets) and runs the
- * contraction on the matrix cores, x and Combined entering as high + low
- * bf16 parts (fp32-level accuracy); TS_F32 weights run the single-token
- * kernels per token, and so does a TS_BF16 batch above 64 whose report asks
- * for the union counts (they need a single pass).
+ * TS_BF16 weights runs the contraction on the matrix cores, x and Combined
+ * entering as high + low bf16 parts (fp32-level accuracy): up to 16 tokens
+ * read the W_up rows of the union of the tokens' open gates, above that
+ * every W_up row is read (nearly all are in the union), and the W_down rows
+ * of the union of the active sets; each row once for up to 128 tokens.
+ * TS_F32 weights run the single-token kernels per token, and so does a
+ * TS_BF16 batch above 64 whose report asks for the union counts.
  */
 ts_status ts_ffn_sparse(const float *x, const void *w_gate, const void *w_up, const void *w_down_t,
                         ts_dtype wdtype, int batch, int hidden, int inter, float *out,
@@ -216,10 +217,11 @@ size_t ts_moe_workspace_bytes(int batch, int hidden, int inter, int n_experts, i
  *   ws / ws_bytes / stream as above.
  * The routing decision never leaves the device.  Batch 1 (and TS_F32
  * weights) run the pipelined single-token kernel, each workgroup computing
- * its token's router; 2 <= batch <= 64 with TS_BF16 weights run the
- * matrix-core path, each expert's tokens in groups of about twice the
- * expected load (an expert drawing more takes further groups and reads its
- * weights once more per group).
+ * its token's router; batches with TS_BF16 weights run the matrix-core
+ * path, each expert's tokens in groups of about twice the expected load (an
+ * expert drawing more takes further groups and reads its weights once more
+ * per group), above 64 tokens in groups of 64 with x and Combined in three
+ * bf16 parts (all 24 bits).
  */
 ts_status ts_moe_sparse(const float *x, const void *w_router, const void *w_gate, const void *w_up,
                         const void *w_down_t, ts_dtype wdtype, int batch, int hidden, int inter,
@@ -327,6 +329,10 @@ ts_status ts_probe_copy(const void *src, void *dst, size_t bytes, void *stream);
  *                kernel, one copy of x for all expert groups), 1 = a
  *                dispatch kernel builds per-group x fragments (as the
  *                batched FFN does)
+ *   "bx_wide"    batched FFN above 16 tokens and MoE layer above 64:
+ *                0 default (the workgroup-tiled kernels where their plan
+ *                fits the workspace), 1 = passes of up to 64 tokens on the
+ *                other batched kernels (MoE: the single-token kernels)
  *   "ffn_interleave" single-token kernels: 0 default (workgroup t takes
  *                neurons t, t + T, t + 2 T, ... of T workgroups per token,
  *                so the grid streams one narrow band of each matrix at a

@@ -44,58 +44,13 @@
 #include <type_traits>
 
 #include "ts_batch.h"
+#include "ts_bx.h"
 #include "ts_device.h"
 #include "ts_plan.h"
 #include "ts_runtime.h"
 #include "turbosparse.h"
 
 namespace ts {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ f32x4 mfma_bf16(const u32x4 a, const u32x4 b, const f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                   0, 0, 0);
-}
-
-// Shape constants per token-slot count TOK (8, 16, 32, 64).
-template <int TOK>
-struct Bx {
-    static constexpr bool PACK = TOK == 8;          // high and low parts share one 16-column tile
-    static constexpr int NT = PACK ? 1 : TOK / 16;  // 16-token accumulator tiles
-    static constexpr int NX = PACK ? 1 : 2 * NT;    // operand fragments per 32-wide k-step (x or Combined)
-    // k-steps per batch of gate / up loads (default; measured: 2 at 8 token
-    // slots, 4 at 16, 2 past that, where deeper rings spill)
-    static constexpr int KS = PACK ? 2 : (NX <= 2 ? 4 : 2);
-    static constexpr int D = 2;                     // gate / up batches in flight per wave (default)
-    static constexpr int DD = 2;                    // down blocks in flight per wave (default)
-};
-
-struct BxArgs {
-    const float *x;          // [tokens][H] (already offset to the pass's first token)
-    const void *wg, *wu, *wd;
-    size_t expert_stride;    // elements per expert matrix (0: one weight set)
-    int B, H, I, G, K, bpad, hpad, ntiles, nslices, nchunks, tpc;
-    int vpe;                 // groups per weight set: group g uses weight set g / vpe
-    const int32_t *topk;     // [B][K] routed experts, or null (FFN)
-    const float *topw;       // [B][K] routing weights, or null
-    int32_t *gcount;         // [G]
-    int32_t *tslot;          // [B][K][2] (group, slot) of each routed token
-    uint16_t *xhl;           // x fragments [G][hpad / 32][NX][64 lanes][8] bf16 (MFMA operand order)
-    int32_t *cnt;            // [G][ntiles][2] |union G|, |union A|
-    uint8_t *arow;           // [G][ntiles][32] row within the tile of each active slot (slot 0's past |union A|)
-    uint16_t *hfrag;         // [G][ntiles][32 slots][2][bpad] Combined per active slot, bf16 high / low
-    uint32_t *gmask;         // [G][ntiles][bpad] open-gate rows of the tile per token
-    uint32_t *amask;         // [G][ntiles][bpad] active rows of the tile per token
-    float *partial;          // [G][bpad][nchunks][H]
-    float *out;              // [tokens][H]
-    int want_masks;
-    int dense;               // 1: every row is taken (the dense comparator)
-    const uint16_t *xtok;    // or null: every token's x as bf16 high / low parts, token-major (the MoE
-                             // router's split: per token xchunks chunks of 8 values, 32 bytes each)
-    int xchunks;
-};
 
 // x operand source of the gate / up K loop: the per-group fragments built by
 // bx_prep (frag), or (GATHER) this lane's columns gathered from the
@@ -135,37 +90,6 @@ __device__ __forceinline__ BxX<Bx<TOK>::NX> bx_xsource(const BxArgs &a, int g, i
         for (int f = 0; f < NX; ++f) xs.off[f] = kOutOfRange;
     }
     return xs;
-}
-
-// Group g's token list (MoE): the tokens routed to expert g / vpe, entries
-// [r0, r0 + TOK) of that expert's ascending list, by one wave scanning the
-// (token, rank) pairs in token-major order; s_tok[slot] = token, -1 past the
-// count.  With `tables`, also the group's token count and the (group, slot)
-// of each of its routed pairs (for the reduce and the report).  Returns the
-// count (on every lane).
-template <int TOK>
-__device__ __forceinline__ int bx_list_group(const BxArgs &a, int g, int lane, int *s_tok, bool tables) {
-    const int np = a.B * a.K;
-    const int e = g / a.vpe, r0 = (g - e * a.vpe) * TOK;
-    int base = 0;
-    for (int p0 = 0; p0 < np; p0 += 64) {
-        const int p = p0 + lane;
-        const bool mine = p < np && a.topk[p] == e;
-        const uint64_t m = __ballot(mine);
-        const int rank = base + lane_prefix(m, lane) - r0;  // rank within this group
-        if (mine && rank >= 0 && rank < TOK) {
-            s_tok[rank] = p / a.K;
-            if (tables) {
-                a.tslot[p * 2] = g;
-                a.tslot[p * 2 + 1] = rank;
-            }
-        }
-        base += __popcll(m);
-    }
-    const int n = min(max(base - r0, 0), TOK);
-    for (int sl = n + lane; sl < TOK; sl += 64) s_tok[sl] = -1;
-    if (tables && lane == 0) a.gcount[g] = n;
-    return n;
 }
 
 // ---------------------------------------------------------------------------
@@ -395,22 +319,6 @@ __device__ __forceinline__ void bx_token_masks(const bool (&pred)[2][NT][4], con
         m |= (uint32_t)__shfl_xor((int)m, 32, 64);
         tm[nt] = m;
     }
-}
-
-// Position of the n-th (from 0) set bit of m, by halving with population
-// counts; n < popcount(m) (otherwise some position in 0..31).
-__device__ __forceinline__ int nth_set_bit(uint32_t m, int n) {
-    int pos = 0;
-#pragma unroll
-    for (int w = 16; w >= 1; w >>= 1) {
-        const int c = __popc(m & ((1u << w) - 1u));
-        if (n >= c) {
-            n -= c;
-            m >>= w;
-            pos += w;
-        }
-    }
-    return pos;
 }
 
 template <int TOK, int KS, int D, bool GATHER = false>
@@ -912,8 +820,6 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up64(BxArgs a)
 // row load zeros (out-of-range buffer offset) with zero Combined.  Loads of the next DD - 1
 // blocks are in flight while a block is contracted; the four waves' sums
 // are added in a fixed order at the end.
-constexpr uint32_t kPadRow = 0xFFFFFFFFu;  // row-list padding of bx_down
-
 template <int TOK, int DD>
 __global__ __launch_bounds__(256, TOK <= 16 ? 2 : 1) void bx_down(BxArgs a) {
     using S = Bx<TOK>;
@@ -1367,7 +1273,16 @@ ts_status run_batch(const float *x, const void *wg, const void *wu, const void *
     const bool want_lists = stats && (stats->n_gate || stats->n_active || stats->gate_idx || stats->active_idx);
     a.want_masks = want_lists ? 1 : 0;
 
-    switch (p.tok) {
+    a.act = 0;
+    a.tau = 0.f;
+    if (p.wide) {
+        if (!a.topk) launch_wide_prep(p, a, st);
+        // (the "bx_gate" knob compares the one-pass kernels' gate + up: same operands, same bits)
+        if (tuned("bx_gate") == 0 || p.tok > 64 || a.topk) launch_wide_gate_up(p, a, st);
+        else if (p.tok == 64) launch_gate_up<64>(p, a, st);
+        else launch_gate_up<32>(p, a, st);
+        launch_wide_down(p, a, st);
+    } else switch (p.tok) {
     case 8: launch_tok<8>(p, a, st); break;
     case 16: launch_tok<16>(p, a, st); break;
     case 32: launch_tok<32>(p, a, st); break;

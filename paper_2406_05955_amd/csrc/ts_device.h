@@ -144,6 +144,15 @@ __device__ __forceinline__ void split_hi_lo(float x, uint32_t &hi, uint32_t &lo)
     lo = bf16_bits(x - __uint_as_float(hi << 16));
 }
 
+// The open-gate threshold and the Combined activation of a neuron whose
+// gate passed it: act 0 = dReLU (Eq. drelu), 1 = gate-only ReLU with
+// threshold tau.
+__device__ __forceinline__ float gate_threshold(int act, float tau) { return act ? tau : 0.f; }
+__device__ __forceinline__ bool combined_nonzero(int act, float u) { return act ? u != 0.f : u > 0.f; }
+__device__ __forceinline__ float combined_value(int act, float tau, float g, float u) {
+    return act ? (g - tau) * u : g * u;
+}
+
 __device__ __forceinline__ int lane_prefix(uint64_t mask, int lane) {
     return __popcll(mask & ((1ull << lane) - 1ull));
 }

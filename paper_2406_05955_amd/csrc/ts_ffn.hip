@@ -147,14 +147,6 @@ struct SlotArgs {
     int rstride;
 };
 
-// The open-gate threshold and the Combined activation of a neuron whose
-// gate passed it, for either activation.
-__device__ __forceinline__ float gate_threshold(int act, float tau) { return act ? tau : 0.f; }
-__device__ __forceinline__ bool combined_nonzero(int act, float u) { return act ? u != 0.f : u > 0.f; }
-__device__ __forceinline__ float combined_value(int act, float tau, float g, float u) {
-    return act ? (g - tau) * u : g * u;
-}
-
 // The router's decision for one token (section 6.2: top-k gating over the
 // softmax of the router logits), by one wave: softmax over the E (<= 64)
 // logits, the top K (strictly larger wins, so the lower index wins exact
@@ -1805,14 +1797,14 @@ __global__ __launch_bounds__(256) void ffn_union_count(const int32_t *__restrict
 // each wave dots two expert rows at a time (all loads in flight), then
 // wave 0 takes the softmax, the top-k and the renormalised weights
 // (route_wave).  With xs set (bf16 weights, the batched path), the block
-// also writes its token's x as bf16 high / low parts for the matrix cores:
-// row t of xs holds xs_chunks chunks of 8 values (k = 8 c .. 8 c + 7), each
-// 32 bytes (the 8 high parts, then the 8 low parts), zero past H.
+// also writes its token's x as xs_parts (2 or 3) bf16 parts for the matrix
+// cores: row t of xs holds xs_chunks chunks of 8 values (k = 8 c .. 8 c + 7),
+// each 16 xs_parts bytes (the 8 high parts, then the next parts), zero past H.
 template <typename WT, int NC>
 __global__ __launch_bounds__(256) void moe_router(const float *__restrict__ x, const WT *__restrict__ wr, int H,
                                                   int E, int K, int32_t *__restrict__ topk_idx,
                                                   float *__restrict__ topk_w, uint16_t *__restrict__ xs,
-                                                  int xs_chunks) {
+                                                  int xs_chunks, int xs_parts) {
     constexpr int CE = WTraits<WT>::CE;
     constexpr int R = NC >= 16 ? 1 : 2;
     __shared__ float s_l[kMaxExperts];
@@ -1824,28 +1816,29 @@ __global__ __launch_bounds__(256) void moe_router(const float *__restrict__ x, c
     if constexpr (CE == 8) {
         if (xs) {
             // every wave holds all of x; wave w writes the chunks c0 = w mod 4
-            u32x4 *row = reinterpret_cast<u32x4 *>(xs + (size_t)t * xs_chunks * 16);
+            u32x4 *row = reinterpret_cast<u32x4 *>(xs) + (size_t)t * xs_chunks * xs_parts;
 #pragma unroll
             for (int c0 = 0; c0 < NC; ++c0) {
                 const int c = lane + 64 * c0;
                 if ((c0 & 3) == wave && c < nch) {
-                    uint32_t hi[4], lo[4];
+                    float r[8];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        uint32_t h0, l0, h1, l1;
-                        split_hi_lo(xr[c0][2 * e], h0, l0);
-                        split_hi_lo(xr[c0][2 * e + 1], h1, l1);
-                        hi[e] = h0 | (h1 << 16);
-                        lo[e] = l0 | (l1 << 16);
+                    for (int e = 0; e < 8; ++e) r[e] = xr[c0][e];
+                    for (int p = 0; p < xs_parts; ++p) {
+                        uint32_t o[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const uint32_t b0 = bf16_bits(r[2 * e]), b1 = bf16_bits(r[2 * e + 1]);
+                            o[e] = b0 | (b1 << 16);
+                            r[2 * e] -= __uint_as_float(b0 << 16);  // exact
+                            r[2 * e + 1] -= __uint_as_float(b1 << 16);
+                        }
+                        row[xs_parts * c + p] = u32x4{o[0], o[1], o[2], o[3]};
                     }
-                    row[2 * c] = u32x4{hi[0], hi[1], hi[2], hi[3]};
-                    row[2 * c + 1] = u32x4{lo[0], lo[1], lo[2], lo[3]};
                 }
             }
-            for (int c = nch + (int)threadIdx.x; c < xs_chunks; c += 256) {
-                row[2 * c] = u32x4{0u, 0u, 0u, 0u};
-                row[2 * c + 1] = u32x4{0u, 0u, 0u, 0u};
-            }
+            for (int c = nch * xs_parts + (int)threadIdx.x; c < xs_chunks * xs_parts; c += 256)
+                row[c] = u32x4{0u, 0u, 0u, 0u};
         }
     }
     // every block reads all router rows: cached loads, and the blocks that
@@ -1985,15 +1978,15 @@ ts_status launch_reduce(const float *partial, int rows, const SlotPlan &p, const
 
 template <typename WT>
 void launch_router(int nc, int batch, hipStream_t st, const float *x, const void *wr, int H, int E, int K,
-                   int32_t *ridx, float *rw, uint16_t *xs = nullptr, int xs_chunks = 0) {
+                   int32_t *ridx, float *rw, uint16_t *xs = nullptr, int xs_chunks = 0, int xs_parts = 2) {
     const WT *w = static_cast<const WT *>(wr);
     const dim3 g((unsigned)batch), b(256);
     switch (nc) {
-    case 1: launch("moe_router", moe_router<WT, 1>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks); break;
-    case 2: launch("moe_router", moe_router<WT, 2>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks); break;
-    case 4: launch("moe_router", moe_router<WT, 4>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks); break;
-    case 8: launch("moe_router", moe_router<WT, 8>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks); break;
-    default: launch("moe_router", moe_router<WT, 16>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks); break;
+    case 1: launch("moe_router", moe_router<WT, 1>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks, xs_parts); break;
+    case 2: launch("moe_router", moe_router<WT, 2>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks, xs_parts); break;
+    case 4: launch("moe_router", moe_router<WT, 4>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks, xs_parts); break;
+    case 8: launch("moe_router", moe_router<WT, 8>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks, xs_parts); break;
+    default: launch("moe_router", moe_router<WT, 16>, g, b, st, x, w, H, E, K, ridx, rw, xs, xs_chunks, xs_parts); break;
     }
 }
 
@@ -2326,19 +2319,21 @@ ts_status moe_impl(const float *x, const void *wr, const void *wg, const void *w
     float *rw = topk_w ? topk_w : ws_at<float>(ws, roff + align_up256((size_t)batch * K * sizeof(int32_t)));
     BatchPlan bp;
     const size_t estride = (size_t)inter * (size_t)hidden;
-    const bool batched = batch > 1 && tuned("batch_path") == 0 && plan_batch(batch, hidden, inter, E, K, dt, &bp);
+    const bool batched = batch > 1 && tuned("batch_path") == 0 &&
+                         (plan_batch(batch, hidden, inter, E, K, dt, &bp) ||
+                          plan_wide_moe(batch, hidden, inter, E, K, dt, &bp));
     // on the pipelined kernel each workgroup routes its own token (no router launch)
     const bool fold = !batched && slots_use_pipe(p, dense);
     // batched: the router also writes each token's x split for the matrix
     // cores, and the gate+up kernel gathers its group's tokens from it (no
     // dispatch kernel, one copy of x in L2 for all expert groups)
-    const bool xtok = batched && tuned("bx_xtok") == 0;
+    const bool xtok = batched && (bp.batch > kBxMaxTokens || tuned("bx_xtok") == 0);
     if (!fold) {
         if (dt == TS_F32) {
             launch_router<float>(p.nc, batch, st, x, wr, hidden, E, K, ridx, rw);
         } else {
             launch_router<uint16_t>(p.nc, batch, st, x, wr, hidden, E, K, ridx, rw,
-                                    xtok ? ws_at<uint16_t>(ws, bp.off_xhl) : nullptr, bp.hpad / 8);
+                                    xtok ? ws_at<uint16_t>(ws, bp.off_xhl) : nullptr, bp.hpad / 8, bp.parts);
         }
         s = check_launch("moe_router");
         if (s != TS_OK) return s;
@@ -2432,11 +2427,15 @@ ts_status ts_ffn_sparse(const float *x, const void *w_gate, const void *w_up, co
                                      ws_bytes, &p);
     if (s != TS_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Several tokens with bf16 weights: the batched matrix-core path, in
-    // passes of up to 64 tokens (the union count needs a single pass);
-    // shapes it does not take run the single-token kernels per token.
+    // Several tokens with bf16 weights: the batched matrix-core path (above
+    // 16 tokens its wide kernels where their plan fits, otherwise passes of
+    // up to 64 tokens); shapes it does not take, and union counts above 64
+    // tokens, run the single-token kernels per token.
     const bool one_pass = batch <= ts::kBxMaxTokens;
     ts::BatchPlan probe;
+    if ((one_pass || !(stats && stats->n_union)) && ts::tuned("batch_path") == 0 &&
+        ts::plan_wide_ffn(batch, hidden, inter, wdtype, &probe))
+        return ts::run_batch(x, w_gate, w_up, w_down_t, 0, nullptr, nullptr, probe, out, stats, 0, ws, st, false);
     if (batch > 1 && wdtype == TS_BF16 && ts::tuned("batch_path") == 0 &&
         (one_pass || !(stats && stats->n_union)) &&
         ts::plan_batch(std::min(batch, ts::kBxMaxTokens), hidden, inter, 1, 1, wdtype, &probe)) {
@@ -2493,6 +2492,8 @@ ts_status ts_ffn_dense(const float *x, const void *w_gate, const void *w_up, con
     if (s != TS_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     ts::BatchPlan probe;
+    if (ts::tuned("batch_path") == 0 && ts::plan_wide_ffn(batch, hidden, inter, wdtype, &probe))
+        return ts::run_batch(x, w_gate, w_up, w_down_t, 0, nullptr, nullptr, probe, out, nullptr, 0, ws, st, true);
     if (batch > 1 && wdtype == TS_BF16 && ts::tuned("batch_path") == 0 &&
         ts::plan_batch(std::min(batch, ts::kBxMaxTokens), hidden, inter, 1, 1, wdtype, &probe)) {
         for (int t0 = 0; t0 < batch; t0 += ts::kBxMaxTokens) {

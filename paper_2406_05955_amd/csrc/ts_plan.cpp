@@ -19,6 +19,7 @@ std::atomic<int> g_bx_down{0};
 std::atomic<int> g_bx_vgroup{0};
 std::atomic<int> g_interleave{0};
 std::atomic<int> g_bx_xtok{0};
+std::atomic<int> g_bx_wide{0};
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 int esize(ts_dtype dt) { return dt == TS_F32 ? 4 : 2; }
@@ -40,6 +41,7 @@ int tuned(const char *key) {
     if (std::strcmp(key, "bx_vgroup") == 0) return g_bx_vgroup.load();
     if (std::strcmp(key, "ffn_interleave") == 0) return g_interleave.load();
     if (std::strcmp(key, "bx_xtok") == 0) return g_bx_xtok.load();
+    if (std::strcmp(key, "bx_wide") == 0) return g_bx_wide.load();
     return 0;
 }
 
@@ -194,6 +196,35 @@ bool plan_slots(int hidden, int inter, ts_dtype dt, int slots, int slots_per_out
     return true;
 }
 
+namespace {
+// Workspace regions of a batched plan.
+void batch_layout(BatchPlan &q) {
+    const size_t P = (size_t)q.parts, G = (size_t)q.groups, T = (size_t)q.ntiles;
+    size_t off = 0;
+    q.off_gcount = off;  // tokens per group
+    off = align256(off + G * sizeof(int32_t));
+    q.off_tslot = off;   // (group, slot) of each (token, routed rank)
+    off = align256(off + (size_t)q.batch * q.top_k * 2 * sizeof(int32_t));
+    q.off_xhl = off;     // x in bf16 parts: [G][parts][tok][hpad]
+    off = align256(off + G * P * q.tok * q.hpad * sizeof(uint16_t));
+    q.off_cnt = off;     // per tile: |union G|, |union A|
+    off = align256(off + G * T * 2 * sizeof(int32_t));
+    q.off_arow = off;    // per tile: row (within the tile) of each of its 32 active slots, bytes
+    off = align256(off + G * T * kBxRows);
+    q.off_hfrag = off;   // per tile: Combined in bf16 parts, [2][tok][32 slots]
+    off = align256(off + G * T * P * q.tok * kBxRows * sizeof(uint16_t));
+    q.off_gmask = off;   // per tile and token: open-gate rows (bit mask)
+    off = align256(off + G * T * q.tok * sizeof(uint32_t));
+    q.off_amask = off;   // per tile and token: active rows (bit mask)
+    off = align256(off + G * T * q.tok * sizeof(uint32_t));
+    q.off_partial = off; // down partials: [G][tok][nchunks][hidden]
+    off = align256(off + G * q.tok * (size_t)q.nchunks * q.hidden * sizeof(float));
+    q.off_union = off;
+    off = align256(off + 4 * sizeof(int32_t));
+    q.total = off;
+}
+}  // namespace
+
 bool plan_batch(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt, BatchPlan *p) {
     if (check_dims(batch, hidden, inter, dt) != TS_OK || dt != TS_BF16 || experts < 1 || top_k < 1) return false;
     if (batch > kBxMaxTokens) return false;
@@ -226,31 +257,66 @@ bool plan_batch(int batch, int hidden, int inter, int experts, int top_k, ts_dty
     q.nchunks = std::max(1, std::min(want, q.ntiles));
     q.tpc = std::min((q.ntiles + q.nchunks - 1) / q.nchunks, bx_down_tiles(q.tok));
     q.nchunks = (q.ntiles + q.tpc - 1) / q.tpc;
-    const size_t G = (size_t)groups, T = (size_t)q.ntiles;
-    size_t off = 0;
-    q.off_gcount = off;  // tokens per group
-    off = align256(off + G * sizeof(int32_t));
-    q.off_tslot = off;   // (group, slot) of each (token, routed rank)
-    off = align256(off + (size_t)batch * top_k * 2 * sizeof(int32_t));
-    q.off_xhl = off;     // x split into bf16 high and low parts: [G][2][tok][hpad]
-    off = align256(off + G * 2 * q.tok * q.hpad * sizeof(uint16_t));
-    q.off_cnt = off;     // per tile: |union G|, |union A|
-    off = align256(off + G * T * 2 * sizeof(int32_t));
-    q.off_arow = off;    // per tile: row (within the tile) of each of its 32 active slots, bytes
-    off = align256(off + G * T * kBxRows);
-    q.off_hfrag = off;   // per tile: Combined as bf16 high / low, [2][tok][32 slots]
-    off = align256(off + G * T * 2 * q.tok * kBxRows * sizeof(uint16_t));
-    q.off_gmask = off;   // per tile and token: open-gate rows (bit mask)
-    off = align256(off + G * T * q.tok * sizeof(uint32_t));
-    q.off_amask = off;   // per tile and token: active rows (bit mask)
-    off = align256(off + G * T * q.tok * sizeof(uint32_t));
-    q.off_partial = off; // down partials: [G][tok][nchunks][hidden]
-    off = align256(off + G * q.tok * (size_t)q.nchunks * hidden * sizeof(float));
-    q.off_union = off;
-    off = align256(off + 4 * sizeof(int32_t));
-    q.total = off;
+    batch_layout(q);
     *p = q;
     return true;
+}
+
+namespace {
+
+// Wide plan: experts x ceil(batch / tok) groups of `tok` slots, within
+// `limit` workspace bytes (fewer down chunks where that helps).
+bool plan_wide(int batch, int hidden, int inter, int experts, int top_k, int tok, int parts, ts_dtype dt,
+               size_t limit, BatchPlan *p) {
+    if (dt != TS_BF16 || g_bx_wide.load() == 1) return false;
+    // row offsets are 32-bit byte offsets into one matrix
+    if ((unsigned long long)inter * (unsigned long long)hidden * 2ull >= (1ull << 32) - 16) return false;
+    BatchPlan q;
+    q.wide = true;
+    q.parts = parts;
+    q.batch = batch;
+    q.hidden = hidden;
+    q.inter = inter;
+    q.top_k = top_k;
+    q.experts = experts;
+    q.tok = tok;
+    q.vpe = (batch + tok - 1) / tok;
+    q.groups = experts * q.vpe;
+    q.bpad = tok;
+    q.hpad = (hidden + kBxKQuant - 1) / kBxKQuant * kBxKQuant;
+    q.ntiles = (inter + kBxRows - 1) / kBxRows;
+    q.nslices = (hidden + wd_slice_cols(tok, parts) - 1) / wd_slice_cols(tok, parts);
+    const int busy = experts > 1 ? experts : q.groups;  // (an expert's further groups are nearly always empty)
+    int want = g_down_chunks.load();
+    // one down workgroup per compute unit, two at 32 tokens (25.2 against 30.5 us)
+    if (want <= 0) want = std::max(1, (tok == 32 ? 512 : 256) / (q.nslices * busy));
+    for (; want >= 1; want /= 2) {
+        q.nchunks = std::min(want, q.ntiles);
+        q.tpc = std::min((q.ntiles + q.nchunks - 1) / q.nchunks, wd_down_tiles(tok, parts));
+        q.nchunks = (q.ntiles + q.tpc - 1) / q.tpc;
+        batch_layout(q);
+        if (q.total <= limit) {
+            *p = q;
+            return true;
+        }
+    }
+    return false;
+}
+
+}  // namespace
+
+bool plan_wide_ffn(int batch, int hidden, int inter, ts_dtype dt, BatchPlan *p) {
+    if (check_dims(batch, hidden, inter, dt) != TS_OK || batch <= kWdMinTokens) return false;
+    const int tok = batch <= 32 ? 32 : (batch <= 64 ? 64 : 128);
+    return plan_wide(batch, hidden, inter, 1, 1, tok, 2, dt, ffn_ws_bytes(batch, hidden, inter, dt), p);
+}
+
+// Three parts: these calls' other route is the single-token kernels, whose
+// products are fp32.
+bool plan_wide_moe(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt, BatchPlan *p) {
+    if (check_moe_dims(batch, hidden, inter, experts, top_k, dt) != TS_OK || batch <= kBxMaxTokens) return false;
+    return plan_wide(batch, hidden, inter, experts, top_k, 64, 3, dt,
+                     moe_route_offset(batch, hidden, inter, experts, top_k, dt), p);
 }
 
 // Chunk of list entries per workgroup: enough workgroups for one per compute
@@ -409,6 +475,11 @@ ts_status ts_tune_set(const char *key, int value) {
     if (std::strcmp(key, "bx_xtok") == 0) {
         if (value < 0 || value > 1) return TS_ERR_SHAPE;
         ts::g_bx_xtok.store(value);
+        return TS_OK;
+    }
+    if (std::strcmp(key, "bx_wide") == 0) {
+        if (value < 0 || value > 1) return TS_ERR_SHAPE;
+        ts::g_bx_wide.store(value);
         return TS_OK;
     }
     return TS_ERR_SHAPE;

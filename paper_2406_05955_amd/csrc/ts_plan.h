@@ -124,11 +124,29 @@ struct BatchPlan {
     int ntiles = 0;      // 32-neuron tiles per group
     int nslices = 0;     // 128-column slices of the down kernel
     int nchunks = 0;     // tile chunks per group in the down kernel
-    int tpc = 0;         // tiles per chunk (<= bx_down_tiles(tok))
+    int tpc = 0;         // tiles per chunk (<= bx_down_tiles(tok), wide: wd_down_tiles)
+    bool wide = false;   // the workgroup-tiled kernels of ts_wide.hip
+    int parts = 2;       // bf16 parts of x and Combined (3: all 24 bits)
     size_t off_gcount = 0, off_tslot = 0, off_xhl = 0, off_cnt = 0, off_arow = 0, off_hfrag = 0;
     size_t off_gmask = 0, off_amask = 0, off_partial = 0, off_union = 0;
     size_t total = 0;
 };
+
+// Wide batches: the workgroup-tiled kernels, for the FFN above kWdMinTokens
+// tokens (32 tokens 79 against 95 us per Mistral layer, 64 tokens 100
+// against 137, 256 tokens 197 against 527; at 16 the kernels of
+// ts_batch.hip read only the open W_up rows and are not bound by x) and for
+// the MoE layer above kBxMaxTokens.  A plan is taken only where it fits the
+// workspace that the shape's other plans need, so workspace sizes do not
+// depend on it.
+constexpr int kWdMinTokens = 16;
+// 32-row tiles per down workgroup at most: its row list shares LDS with the
+// staging (the three-part MoE kernel: half a 14336-neuron expert, as bx_down).
+constexpr int wd_down_tiles(int tok, int parts) { return tok <= 64 && parts == 3 ? 224 : 64; }
+// Output columns per down workgroup.
+constexpr int wd_slice_cols(int tok, int parts) { return tok > 64 || parts == 3 ? 256 : 128; }
+bool plan_wide_ffn(int batch, int hidden, int inter, ts_dtype dt, BatchPlan *p);
+bool plan_wide_moe(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt, BatchPlan *p);
 
 // Given-list path (ts_ffn_sparse_given): each token's list is cut into
 // chunks of `chunk` entries, one pipelined workgroup per (token, chunk).

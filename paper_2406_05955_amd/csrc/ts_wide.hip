@@ -1,0 +1,721 @@
+// Batched activation-sparse dReLU FFN for gfx950 where a weight set has many
+// tokens: workgroup-tiled matrix-core kernels whose operands are shared
+// through LDS by all waves of a workgroup.
+//
+// The kernels of ts_batch.hip let every wave contract its own quarter of the
+// hidden dimension for all rows and tokens of a workgroup: no barrier in the
+// K loop, but each wave holds every accumulator, so a workgroup takes at
+// most 64 rows x 64 tokens, and more tokens mean another pass over the
+// weights.  Here the eight waves split the workgroup's rows and tokens, the
+// K loop stages both operands in LDS once per workgroup (double buffered,
+// the next stages' loads in registers), and:
+//   wd_gate_up   a workgroup takes NB neurons' W_gate and W_up rows together
+//                against up to TOK tokens: one pass over the x fragments for
+//                both matrices, gate and up of a neuron end in the same
+//                lane, and Combined leaves the kernel as in ts_batch.hip
+//                (active rows of each 32-row tile as slots).  Every W_up row
+//                is read: with this many tokens nearly every row is open for
+//                one of them (at 20% open gates 99.9% of the rows at 32
+//                tokens).
+//   wd_down      per (group, chunk of tiles, column slice): K blocks of 32
+//                listed active rows; W_down_t rows and Combined records are
+//                both neuron-major, so both operands are read back from LDS
+//                with transposing reads (ds_read_b64_tr_b16).
+// x and Combined enter as P bf16 parts: 2 (16 significant bits) or 3 (all
+// 24 bits of the fp32 value: products as exact as fp32 ones).
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <type_traits>
+
+#include "ts_bx.h"
+#include "ts_device.h"
+#include "ts_plan.h"
+#include "ts_runtime.h"
+#include "turbosparse.h"
+
+namespace ts {
+
+namespace {
+
+constexpr int kWdThreads = 512;
+
+// Past every buffer resource here (matrices are below 4 GB): a load there
+// returns zeros and touches no memory.
+constexpr uint32_t kWdOob = 0xFFFFFFF0u;
+
+template <bool STREAM>
+__device__ __forceinline__ u32x4 wd_ld(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    if constexpr (STREAM) return ld_buf_stream(r, off);
+    else return ld_buf_cached(r, off);
+}
+
+// 16-byte chunk c of 128-byte LDS row r sits at this position: 16 rows of a
+// fragment read spread over all banks.
+__device__ __forceinline__ int wd_swz(int r, int c) { return r * 8 + (c ^ ((r >> 1) & 7)); }
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+// MFMA operand (lane (lm, lq): eight k's of column lm) out of a k-major LDS
+// tile: two transposing reads, each giving the 16 lanes of one lq four k
+// rows x 16 columns; `p` is the tile's column 0 of the fragment, `pitch` in
+// elements.  Lane group lq takes k rows 4 lq .. 4 lq + 3 and 16 + 4 lq ..
+// (both operands alike, so every product pairs the same k): the rows of one
+// read are consecutive and, with rows padded by 32 bytes, spread over all
+// banks.
+__device__ __forceinline__ u32x4 wd_tr_frag(const uint16_t *p, int pitch, int lane) {
+    const int lm = lane & 15, lq = lane >> 4;
+    const uint16_t *q = p + (4 * lq + (lm >> 2)) * pitch + 4 * (lm & 3);
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(q));
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(q + 16 * pitch));
+    return __builtin_bit_cast(u32x4, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Workgroup barrier that orders LDS only (global loads stay in flight).
+__device__ __forceinline__ void wd_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+}  // namespace
+
+// x of every group's token slots as MFMA operand fragments in P parts (the
+// FFN: group g holds tokens [g TOK, (g + 1) TOK)); fragment P nt + part of
+// k-step ks, lane (lm, lq): the 8 values at k = 32 ks + 8 lq of token slot
+// 16 nt + lm.  One thread per (group, k-step, n-tile, lane): one read of x,
+// P fragments written.
+template <int TOK, int P>
+__global__ __launch_bounds__(256) void wd_prep(BxArgs a) {
+    constexpr int NTT = TOK / 16;
+    const int nks = a.hpad / 32;
+    if (blockIdx.x == 0) {
+        for (int t = threadIdx.x; t < a.B; t += 256) {
+            a.tslot[t * 2] = t / TOK;
+            a.tslot[t * 2 + 1] = t % TOK;
+        }
+        for (int g = threadIdx.x; g < a.G; g += 256) a.gcount[g] = min(TOK, a.B - g * TOK);
+    }
+    const int idx = blockIdx.x * 256 + threadIdx.x;
+    if (idx >= a.G * nks * NTT * 64) return;
+    const int lane = idx & 63, lm = lane & 15, lq = lane >> 4;
+    const int nt = (idx >> 6) % NTT;
+    const int ks = (idx >> 6) / NTT % nks;
+    const int g = (idx >> 6) / (NTT * nks);
+    const int t = g * TOK + 16 * nt + lm;
+    const int k0 = ks * 32 + 8 * lq;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (t < a.B && k0 < a.H) {  // H is a multiple of 8, so all 8 are in range
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(a.x + (size_t)t * a.H + k0);
+        const f32x4 p = src[0], q = src[1];
+        v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w;
+        v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
+    }
+    u32x4 *dst = reinterpret_cast<u32x4 *>(a.xhl) + (((size_t)g * nks + ks) * (P * NTT) + P * nt) * 64 + lane;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        uint32_t o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t b0 = bf16_bits(v[2 * e]), b1 = bf16_bits(v[2 * e + 1]);
+            o[e] = b0 | (b1 << 16);
+            v[2 * e] -= __uint_as_float(b0 << 16);      // exact
+            v[2 * e + 1] -= __uint_as_float(b1 << 16);
+        }
+        dst[p * 64] = u32x4{o[0], o[1], o[2], o[3]};
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Gate + up for NB neurons x TOK token slots per workgroup: 2 NB weight rows
+// (gate rows first) and the x fragments of 64 hidden elements per stage.
+// Waves: 4 along the neurons x 2 along the tokens; a wave's gate and up
+// m-tiles are of the same neurons.  D stages of loads are in flight in
+// registers besides the two LDS buffers.  STREAM: non-temporal weight loads
+// (off where several groups share a weight set: the second group's read of a
+// tile then hits in L2, since both run on one XCD).
+// QSPLIT: the sums of the hidden dimension's quarters are added in
+// bx_gate_up's order, (q0 + q1) + (q2 + q3): the same bits.
+template <int TOK, int P, int NB, int D, bool GATHER, bool STREAM>
+__global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
+    constexpr int KS = 2;                       // 32-wide k-steps per stage
+    constexpr int NX = P * TOK / 16;            // x fragments per k-step
+    constexpr int NA = 2 * NB * 8 / kWdThreads; // weight chunks per thread and stage
+    constexpr int XCH = KS * NX * 64;           // x chunks per stage
+    constexpr int NXL = (XCH + kWdThreads - 1) / kWdThreads;
+    constexpr int MN = NB / 64;                 // neuron m-tiles per wave
+    constexpr int NT = TOK / 32;                // token n-tiles per wave
+    constexpr int NW = NB / kBxRows;            // 32-row tiles per workgroup
+    constexpr bool QSPLIT = TOK <= 64 && P == 2;
+    constexpr int ABUF = 2 * NB * 8, BBUF = XCH;  // 16-byte units per LDS buffer
+    constexpr int SH = NB * P * TOK / 8;          // 16-byte units of the Combined staging
+    constexpr int LDS = 2 * (ABUF + BBUF) > SH ? 2 * (ABUF + BBUF) : SH;
+    static_assert(NA % 2 == 0 && NB % 64 == 0 && TOK % 32 == 0, "gate and up halves, whole wave tiles");
+    __shared__ u32x4 s_lds[LDS];
+    __shared__ uint32_t s_open[NW], s_act[NW];
+    __shared__ uint32_t s_gm[NW][TOK], s_am[NW][TOK];
+    __shared__ int s_tok[GATHER ? TOK : 1];
+    __shared__ int s_ng;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lm = lane & 15, lq = lane >> 4;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int nwt = (a.ntiles + NW - 1) / NW;  // workgroup tiles per group
+    int g, wt;
+    if constexpr (GATHER) {
+        g = bx_group_at(blockIdx.x / nwt, a.G, a.vpe);
+        wt = blockIdx.x % nwt;
+    } else {
+        // groups share the weight set: all groups of a tile on one XCD
+        // (the dispatcher hands workgroup b to XCD b % 8), one after another
+        const int q = blockIdx.x % 8, r = blockIdx.x / 8;
+        g = r % a.G;
+        wt = 8 * (r / a.G) + q;
+        if (wt >= nwt) return;
+    }
+    const int tile0 = wt * NW;
+    const int nsub = min(NW, a.ntiles - tile0);
+    const size_t tix0 = (size_t)g * a.ntiles + tile0;
+    int ng;
+    if constexpr (GATHER) {
+        if (wave == 0) {
+            const int n = bx_list_group<TOK>(a, g, lane, s_tok, wt == 0);
+            if (lane == 0) s_ng = n;
+        }
+        __syncthreads();
+        ng = s_ng;
+    } else {
+        ng = a.gcount[g];
+    }
+    if (ng == 0) {
+        if (tid < 2 * nsub) a.cnt[tix0 * 2 + tid] = 0;
+        if (a.want_masks)
+            for (int s = tid; s < nsub * TOK; s += kWdThreads) {
+                a.gmask[tix0 * TOK + s] = 0;
+                a.amask[tix0 * TOK + s] = 0;
+            }
+        return;
+    }
+    if (tid < NW) {
+        s_open[tid] = 0u;
+        s_act[tid] = 0u;
+    }
+    for (int e = tid; e < NW * TOK; e += kWdThreads) {
+        (&s_gm[0][0])[e] = 0u;
+        (&s_am[0][0])[e] = 0u;
+    }
+
+    const int H = a.H, r0 = tile0 * kBxRows;
+    const uint32_t mbytes = (uint32_t)a.I * (uint32_t)H * 2u;
+    const size_t eoff = (size_t)(g / a.vpe) * a.expert_stride;
+    const __amdgpu_buffer_rsrc_t rwg = make_rsrc(reinterpret_cast<const uint16_t *>(a.wg) + eoff, mbytes);
+    const __amdgpu_buffer_rsrc_t rwu = make_rsrc(reinterpret_cast<const uint16_t *>(a.wu) + eoff, mbytes);
+    const int nst = a.hpad / (32 * KS);  // a multiple of 16 (kBxKQuant)
+
+    // this thread's weight chunks: LDS row 64 j + tid / 8, chunk tid % 8
+    const int ac = tid & 7, ar = tid >> 3;
+    uint32_t aoff[NA];
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+        const int row = 64 * (j % (NA / 2)) + ar;
+        aoff[j] = 2u * (uint32_t)min(r0 + row, a.I - 1) * (uint32_t)H + 16u * (uint32_t)ac;
+    }
+    // x chunks: linear in the group's fragments, or gathered from the
+    // token-major split (16 P bytes per 8 values of a token)
+    const u32x4 *xb = reinterpret_cast<const u32x4 *>(a.xhl) + (size_t)g * (a.hpad / 32) * NX * 64;
+    const __amdgpu_buffer_rsrc_t rx =
+        GATHER ? make_rsrc(a.xtok, (uint32_t)a.B * (uint32_t)a.xchunks * 16u * P)
+               : make_rsrc(xb, (uint32_t)(a.hpad / 32) * NX * 1024u);
+    uint32_t xoff[NXL];
+#pragma unroll
+    for (int j = 0; j < NXL; ++j) {
+        const int idx = tid + kWdThreads * j;
+        xoff[j] = kWdOob;
+        if (idx < XCH) {
+            if constexpr (GATHER) {
+                const int l = idx & 63, f = (idx >> 6) % NX, s = (idx >> 6) / NX;
+                const int tk = s_tok[16 * (f / P) + (l & 15)];
+                if (tk >= 0)
+                    xoff[j] = (uint32_t)tk * (uint32_t)a.xchunks * (16u * P) +
+                              (uint32_t)(4 * s + (l >> 4)) * (16u * P) + 16u * (uint32_t)(f % P);
+            } else {
+                if (16 * ((idx >> 6) % NX / P) < ng) xoff[j] = 16u * (uint32_t)idx;
+            }
+        }
+    }
+    constexpr uint32_t XSTEP = GATHER ? KS * 4 * 16 * P : XCH * 16;  // bytes per stage
+
+    u32x4 ra[D][NA], rb[D][NXL];
+    auto issue = [&](int d, int st) {
+        const bool kin = st * 64 + 8 * ac < H;
+#pragma unroll
+        for (int j = 0; j < NA; ++j)
+            ra[d][j] = wd_ld<STREAM>(j < NA / 2 ? rwg : rwu, kin ? aoff[j] + 128u * (uint32_t)st : kWdOob);
+#pragma unroll
+        for (int j = 0; j < NXL; ++j)
+            rb[d][j] = ld_buf_cached(rx, xoff[j] != kWdOob ? xoff[j] + XSTEP * (uint32_t)st : kWdOob);
+    };
+    auto stash = [&](int d, int buf) {
+        u32x4 *sa = s_lds + buf * ABUF, *sb = s_lds + 2 * ABUF + buf * BBUF;
+#pragma unroll
+        for (int j = 0; j < NA; ++j) sa[wd_swz(64 * j + ar, ac)] = ra[d][j];
+#pragma unroll
+        for (int j = 0; j < NXL; ++j)
+            if (XCH % kWdThreads == 0 || tid + kWdThreads * j < XCH) sb[tid + kWdThreads * j] = rb[d][j];
+    };
+    // P == 3 (fp32-exact operands): the high parts' sums apart from the small
+    // lower ones (cgl, cul), so those do not round the large sum
+    constexpr bool LO = P == 3;
+    f32x4 cg[MN][NT], cu[MN][NT], cgl[LO ? MN : 1][LO ? NT : 1], cul[LO ? MN : 1][LO ? NT : 1];
+    auto clear = [&]() {
+#pragma unroll
+        for (int m = 0; m < MN; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) cg[m][n] = cu[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    // the wave's n-tiles are wn, wn + 2, ...; the first NACT hold tokens
+    auto compute = [&](int buf, auto nac) {
+        constexpr int NACT = decltype(nac)::value;
+        const u32x4 *sa = s_lds + buf * ABUF, *sb = s_lds + 2 * ABUF + buf * BBUF;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            u32x4 ag[MN], au[MN];
+#pragma unroll
+            for (int m = 0; m < MN; ++m) {
+                const int row = (wm * MN + m) * 16 + lm;
+                ag[m] = sa[wd_swz(row, 4 * s + lq)];
+                au[m] = sa[wd_swz(NB + row, 4 * s + lq)];
+            }
+#pragma unroll
+            for (int n = 0; n < NACT; ++n) {
+                u32x4 b[P];
+#pragma unroll
+                for (int p = 0; p < P; ++p) b[p] = sb[(s * NX + P * (2 * n + wn) + p) * 64 + lane];
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int m = 0; m < MN; ++m) {
+                        f32x4 &g = LO && p ? cgl[LO ? m : 0][LO ? n : 0] : cg[m][n];
+                        f32x4 &v = LO && p ? cul[LO ? m : 0][LO ? n : 0] : cu[m][n];
+                        g = mfma_bf16(ag[m], b[p], g);
+                        v = mfma_bf16(au[m], b[p], v);
+                    }
+            }
+        }
+    };
+
+    constexpr int U = D > 2 ? D : 2;
+    static_assert(4 % U == 0, "a quarter's stages (a multiple of 4) in whole rounds");
+    clear();
+#pragma unroll
+    for (int d = 0; d < D; ++d) issue(d, d);
+    stash(0, 0);
+    issue(0, D);
+    wd_barrier();
+    // stage st of the ring slot (st mod D): its buffer is contracted, then
+    // the next stage goes from registers to the other buffer and its slot
+    // takes a later stage (loads past the last stage are out of range: zeros)
+    auto steps_n = [&](int s0, int s1, auto nac) {
+        for (int st = s0; st < s1; st += U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                compute(u & 1, nac);
+                stash((u + 1) % D, (u + 1) & 1);
+                issue((u + 1) % D, st + u + 1 + D);
+                wd_barrier();
+            }
+        }
+    };
+    // n-tiles without tokens are left out (rounded up to 0, 1, 2 or 4 tiles)
+    const int nact = max(0, ((ng + 15) / 16 - wn + 1) / 2);
+    auto steps = [&](int s0, int s1) {
+        if constexpr (NT == 1) return steps_n(s0, s1, std::integral_constant<int, 1>{});
+        if constexpr (NT >= 4) {
+            if (nact > 2) return steps_n(s0, s1, std::integral_constant<int, 4>{});
+        }
+        if constexpr (NT >= 2) {
+            if (nact > 1) return steps_n(s0, s1, std::integral_constant<int, 2>{});
+        }
+        if (nact > 0) return steps_n(s0, s1, std::integral_constant<int, 1>{});
+        return steps_n(s0, s1, std::integral_constant<int, 0>{});
+    };
+    if constexpr (LO) {
+        // the high parts' sum folded every 8 stages (512 hidden elements):
+        // shorter chains of roundings (measured: with one chain per quarter
+        // and all parts in it the MoE layer's error was 1.4e-6, the
+        // single-token kernels' is 6e-7)
+        f32x4 tg[MN][NT], tu[MN][NT];
+#pragma unroll
+        for (int m = 0; m < MN; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) tg[m][n] = tu[m][n] = cgl[m][n] = cul[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < nst; s0 += 8) {
+            clear();
+            steps(s0, s0 + 8);
+#pragma unroll
+            for (int m = 0; m < MN; ++m)
+#pragma unroll
+                for (int n = 0; n < NT; ++n) tg[m][n] += cg[m][n], tu[m][n] += cu[m][n];
+        }
+#pragma unroll
+        for (int m = 0; m < MN; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) cg[m][n] = tg[m][n] + cgl[m][n], cu[m][n] = tu[m][n] + cul[m][n];
+    } else if constexpr (QSPLIT) {
+        f32x4 tg[MN][NT], tu[MN][NT], t2g[MN][NT], t2u[MN][NT];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q) clear();
+            steps(q * (nst / 4), (q + 1) * (nst / 4));
+#pragma unroll
+            for (int m = 0; m < MN; ++m)
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    if (q == 0) tg[m][n] = cg[m][n], tu[m][n] = cu[m][n];
+                    else if (q == 1) tg[m][n] += cg[m][n], tu[m][n] += cu[m][n];
+                    else if (q == 2) t2g[m][n] = cg[m][n], t2u[m][n] = cu[m][n];
+                    else {
+                        cg[m][n] = tg[m][n] + (t2g[m][n] + cg[m][n]);
+                        cu[m][n] = tu[m][n] + (t2u[m][n] + cu[m][n]);
+                    }
+                }
+        }
+    } else {
+        steps(0, nst);
+    }
+
+    // ---- open gates, active rows: lane (lm, lq), register i holds neuron
+    // 16 (wm MN + m) + 4 lq + i, token slot 16 (2 n + wn) + lm
+    const float thr = gate_threshold(a.act, a.tau);
+    uint32_t abits[MN];  // this lane's active (neuron i, n) pairs: bit 4 n + i
+#pragma unroll
+    for (int m = 0; m < MN; ++m) {
+        uint32_t ob = 0, ab = 0, obits = 0;
+        abits[m] = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool in = r0 + (wm * MN + m) * 16 + 4 * lq + i < a.I;
+            uint64_t mo = 0, ma = 0;
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                const bool tin = 16 * (2 * n + wn) + lm < ng;
+                const float gv = cg[m][n][i], uv = cu[m][n][i];
+                const bool op = in && tin && gv > thr;
+                const bool on = op && combined_nonzero(a.act, uv);
+                if (a.dense ? in : op) obits |= 1u << (4 * n + i);
+                if (a.dense ? in : on) abits[m] |= 1u << (4 * n + i);
+                mo |= __ballot(a.dense ? in : op);
+                ma |= __ballot(a.dense ? in : on);
+                cg[m][n][i] = on ? combined_value(a.act, a.tau, gv, uv) : 0.f;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if ((mo >> (16 * q)) & 0xFFFFull) ob |= 1u << (4 * q + i);
+                if ((ma >> (16 * q)) & 0xFFFFull) ab |= 1u << (4 * q + i);
+            }
+        }
+        const int mt = wm * MN + m, sh = 16 * (mt & 1);
+        if (lane == 0) {
+            atomicOr(&s_open[mt >> 1], ob << sh);
+            atomicOr(&s_act[mt >> 1], ab << sh);
+        }
+        if (a.want_masks) {
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                const int t = 16 * (2 * n + wn) + lm;
+                atomicOr(&s_gm[mt >> 1][t], ((obits >> (4 * n)) & 15u) << (sh + 4 * lq));
+                atomicOr(&s_am[mt >> 1][t], ((abits[m] >> (4 * n)) & 15u) << (sh + 4 * lq));
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- Combined of every active row into its slot (its rank in the tile)
+    uint16_t *sh16 = reinterpret_cast<uint16_t *>(s_lds);
+#pragma unroll
+    for (int m = 0; m < MN; ++m) {
+        const int mt = wm * MN + m;
+        const uint32_t am = s_act[mt >> 1];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int b = 16 * (mt & 1) + 4 * lq + i;
+            if ((am >> b) & 1u) {
+                const int slot = __popc(am & ((1u << b) - 1u));
+                uint16_t *dst = sh16 + ((mt >> 1) * kBxRows + slot) * (P * TOK);
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    const int t = 16 * (2 * n + wn) + lm;
+                    float v = cg[m][n][i];
+#pragma unroll
+                    for (int p = 0; p < P; ++p) {
+                        const uint32_t h = bf16_bits(v);
+                        dst[p * TOK + t] = (uint16_t)h;
+                        v -= __uint_as_float(h << 16);
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    constexpr int RC = P * TOK / 8;  // 16-byte chunks per record
+    for (int h = 0; h < nsub; ++h) {
+        const uint32_t am = s_act[h];
+        const int na = __popc(am);
+        u32x4 *hdst = reinterpret_cast<u32x4 *>(a.hfrag) + (tix0 + h) * (kBxRows * RC);
+        for (int e = tid; e < na * RC; e += kWdThreads) hdst[e] = s_lds[h * kBxRows * RC + e];
+        if (tid < kBxRows)  // an empty tile lists row 0 (always < I), never used
+            a.arow[(tix0 + h) * kBxRows + tid] = na > 0 ? (uint8_t)nth_set_bit(am, tid < na ? tid : 0) : (uint8_t)0;
+        if (tid == 0) {
+            a.cnt[(tix0 + h) * 2] = __popc(s_open[h]);
+            a.cnt[(tix0 + h) * 2 + 1] = na;
+        }
+        if (a.want_masks)
+            for (int t = tid; t < TOK; t += kWdThreads) {
+                a.gmask[(tix0 + h) * TOK + t] = s_gm[h][t];
+                a.amask[(tix0 + h) * TOK + t] = s_am[h][t];
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Down: workgroup (group, chunk of tiles, slice of CW columns) x all token
+// slots.  The chunk's active rows are listed as in bx_down and cut into K
+// blocks of 32; a block's W_down_t rows and Combined records go through LDS
+// (rows padded by 32 bytes, so a transposing read's four rows start on
+// different banks).  Waves: WC along the columns x 8 / WC along the tokens.
+template <int TOK, int P, int CW, int WC, int KS, int D, int MAXT, bool STREAM>
+__global__ __launch_bounds__(kWdThreads, 2) void wd_down(BxArgs a) {
+    constexpr int WT = 8 / WC;
+    constexpr int NC = CW / 16 / WC, NT = TOK / 16 / WT;  // tiles per wave
+    constexpr int KB = KS * kBxRows;                          // listed rows per block
+    constexpr int WCH = KB * CW / 8, HCH = KB * P * TOK / 8;  // 16-byte chunks per block
+    constexpr int NW = WCH / kWdThreads, NH = (HCH + kWdThreads - 1) / kWdThreads;
+    constexpr int WP = CW + 16, HP = P * TOK + 16;  // LDS row pitches (elements)
+    static_assert(WCH % kWdThreads == 0 && NC >= 1 && NT >= 1, "whole chunks per thread");
+    __shared__ __attribute__((aligned(16))) uint16_t s_w[2][KB * WP], s_h[2][KB * HP];
+    __shared__ uint32_t s_ent[(MAXT + KS - 1) * kBxRows];  // (tile within the chunk) << 10 | slot << 5 | row, or kPadRow
+    __shared__ int s_pre[MAXT + 1];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lm = lane & 15, lq = lane >> 4;
+    const int wc = wave % WC, wtk = wave / WC;
+    // Work item (group, chunk, slice): the slices of a (group, chunk) pair on
+    // one XCD (its Combined records and list in one L2); for groups sharing
+    // a weight set (a.topk null) all groups of a chunk as well (its rows).
+    const int share = a.topk ? 1 : a.vpe;
+    const int nitem = a.nslices * share, npairs = a.G / share * a.nchunks;
+    const int q = blockIdx.x % 8, r = blockIdx.x / 8;
+    const int j8 = r / nitem, it = r % nitem;
+    const int pair = 8 * j8 + ((q - j8) & 7);
+    if (pair >= npairs) return;
+    const int slice = it % a.nslices;
+    const int chunk = pair % a.nchunks;
+    const int gs = pair / a.nchunks;
+    const int g = a.topk ? bx_group_at(gs, a.G, a.vpe) : gs * share + it / a.nslices;
+    const int ng = a.gcount[g];
+    if (ng == 0) return;
+    const int H = a.H;
+    const int t0 = chunk * a.tpc;
+    const int ntc = min(a.tpc, a.ntiles - t0);
+    const size_t tbase = (size_t)g * a.ntiles + t0;
+
+    // ---- the chunk's row list (wave 0 scans the tiles' active counts)
+    if (wave == 0) {
+        int base = 0;
+        for (int t = 0; t < ntc; t += 64) {
+            const int v = t + lane < ntc ? a.cnt[(tbase + t + lane) * 2 + 1] : 0;
+            int inc = v;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int u = __shfl_up(inc, o, 64);
+                if (lane >= o) inc += u;
+            }
+            if (t + lane < ntc) s_pre[t + lane] = base + inc - v;
+            base += __shfl(inc, 63, 64);
+        }
+        if (lane == 0) s_pre[ntc] = base;
+    }
+    __syncthreads();
+    const int total = s_pre[ntc];
+    const int nblk = (total + KB - 1) / KB;
+    for (int e = tid; e < ntc * kBxRows; e += kWdThreads) {
+        const int t = e / kBxRows, s = e % kBxRows;
+        const int base = s_pre[t];
+        if (s < s_pre[t + 1] - base)
+            s_ent[base + s] = ((uint32_t)t << 10) | ((uint32_t)s << 5) | (uint32_t)(a.arow[tbase * kBxRows + e] & 31);
+    }
+    for (int e = total + tid; e < nblk * KB; e += kWdThreads) s_ent[e] = kPadRow;
+    __syncthreads();
+
+    const uint16_t *wde = reinterpret_cast<const uint16_t *>(a.wd) + (size_t)(g / a.vpe) * a.expert_stride;
+    const __amdgpu_buffer_rsrc_t rwd = make_rsrc(wde, (uint32_t)a.I * (uint32_t)H * 2u);
+    const __amdgpu_buffer_rsrc_t rh =
+        make_rsrc(a.hfrag + tbase * (kBxRows * P * TOK), (uint32_t)ntc * (kBxRows * P * TOK * 2u));
+    const int col0 = slice * CW;
+
+    u32x4 rw[D][NW], rr[D][NH];
+    auto issue = [&](int d, int b) {
+        const bool bin = b < nblk;
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            const int idx = tid + kWdThreads * j, row = idx / (CW / 8), c = col0 + 8 * (idx % (CW / 8));
+            const uint32_t e = bin ? s_ent[b * KB + row] : kPadRow;
+            const uint32_t n = (uint32_t)(t0 + (int)(e >> 10)) * kBxRows + (e & 31u);
+            rw[d][j] = wd_ld<STREAM>(rwd, e != kPadRow && c < H ? (n * (uint32_t)H + (uint32_t)c) * 2u : kWdOob);
+        }
+#pragma unroll
+        for (int j = 0; j < NH; ++j) {
+            const int idx = tid + kWdThreads * j, row = idx / (P * TOK / 8), c = idx % (P * TOK / 8);
+            const bool in = bin && (HCH % kWdThreads == 0 || idx < HCH);
+            const uint32_t e = in ? s_ent[b * KB + row] : kPadRow;
+            rr[d][j] = ld_buf_cached(rh, e != kPadRow ? (e >> 5) * (P * TOK * 2u) + 16u * (uint32_t)c : kWdOob);
+        }
+    };
+    auto stash = [&](int d, int buf) {
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            const int idx = tid + kWdThreads * j;
+            *reinterpret_cast<u32x4 *>(&s_w[buf][idx / (CW / 8) * WP + 8 * (idx % (CW / 8))]) = rw[d][j];
+        }
+#pragma unroll
+        for (int j = 0; j < NH; ++j) {
+            const int idx = tid + kWdThreads * j;
+            if (HCH % kWdThreads == 0 || idx < HCH)
+                *reinterpret_cast<u32x4 *>(&s_h[buf][idx / (P * TOK / 8) * HP + 8 * (idx % (P * TOK / 8))]) = rr[d][j];
+        }
+    };
+    constexpr bool LO = P == 3;  // the lower parts' sums apart, as in wd_gate_up
+    f32x4 acc[NC][NT], accl[LO ? NC : 1][LO ? NT : 1];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[c][n] = accl[LO ? c : 0][LO ? n : 0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the wave's n-tiles are wtk, wtk + WT, ...
+    auto compute = [&](int buf, auto nac) {
+        constexpr int NACT = decltype(nac)::value;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            u32x4 wf[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                wf[c] = wd_tr_frag(&s_w[buf][s * kBxRows * WP + 16 * (wc * NC + c)], WP, lane);
+#pragma unroll
+            for (int n = 0; n < NACT; ++n) {
+                u32x4 hf[P];
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+                    hf[p] = wd_tr_frag(&s_h[buf][s * kBxRows * HP + p * TOK + 16 * (n * WT + wtk)], HP, lane);
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        f32x4 &v = LO && p ? accl[LO ? c : 0][LO ? n : 0] : acc[c][n];
+                        v = mfma_bf16(wf[c], hf[p], v);
+                    }
+            }
+        }
+    };
+    constexpr int U = D > 2 ? D : 2;
+    auto blocks = [&](auto nac) {
+        for (int b = 0; b < nblk; b += U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (b + u < nblk) {  // uniform over the workgroup
+                    compute(u & 1, nac);
+                    stash((u + 1) % D, (u + 1) & 1);
+                    issue((u + 1) % D, b + u + 1 + D);
+                    wd_barrier();
+                }
+            }
+        }
+    };
+    if (nblk > 0) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) issue(d, d);
+        stash(0, 0);
+        issue(0, D);
+        wd_barrier();
+        // n-tiles without tokens are left out, as in wd_gate_up
+        const int nact = max(0, ((ng + 15) / 16 - wtk + WT - 1) / WT);
+        if (NT >= 4 && nact > 2) blocks(std::integral_constant<int, NT >= 4 ? 4 : NT>{});
+        else if (NT >= 2 && nact > 1) blocks(std::integral_constant<int, NT >= 2 ? 2 : NT>{});
+        else if (nact > 0) blocks(std::integral_constant<int, 1>{});
+        else blocks(std::integral_constant<int, 0>{});
+    }
+    // lane (lm, lq): columns 4 lq .. 4 lq + 3 of a 16-column tile, token lm
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+        const int t = 16 * (n * WT + wtk) + lm;
+        if (t < ng) {
+            float *prow = a.partial + (((size_t)g * TOK + t) * a.nchunks + chunk) * H;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const int col = col0 + 16 * (wc * NC + c) + 4 * lq;
+                if (col < H)
+                    *reinterpret_cast<f32x4 *>(prow + col) = LO ? acc[c][n] + accl[LO ? c : 0][LO ? n : 0] : acc[c][n];
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+
+namespace {
+
+template <int TOK, int P, int NB, int D>
+void launch_wide_gate(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
+    const int nwt = (p.ntiles + NB / kBxRows - 1) / (NB / kBxRows);
+    const dim3 grid((unsigned)((nwt + 7) / 8 * 8 * p.groups));
+    if (p.groups > 1) launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, false>, grid, dim3(kWdThreads), st, a);
+    else launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, true>, grid, dim3(kWdThreads), st, a);
+}
+
+template <int TOK, int P, int NB, int D>
+void launch_wide_gate_moe(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
+    const int nwt = (p.ntiles + NB / kBxRows - 1) / (NB / kBxRows);
+    launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, true, true>, dim3((unsigned)(p.groups * nwt)), dim3(kWdThreads),
+           st, a);
+}
+
+template <int TOK, int P, int CW, int WC, int KS, int D, int MAXT>
+void launch_wide_down_cw(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
+    const int share = a.topk ? 1 : p.vpe;
+    const dim3 dgrid((unsigned)((p.groups / share * p.nchunks + 7) / 8 * 8 * p.nslices * share));
+    if (share > 1) launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, false>, dgrid, dim3(kWdThreads), st, a);
+    else launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, true>, dgrid, dim3(kWdThreads), st, a);
+}
+
+}  // namespace
+
+void launch_wide_prep(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
+    const dim3 grid((unsigned)((p.groups * (p.hpad / 32) * (p.tok / 16) * 64 + 255) / 256));
+    switch (p.tok) {
+    case 32: launch("batch_prep", wd_prep<32, 2>, grid, dim3(256), st, a); break;
+    case 64: launch("batch_prep", wd_prep<64, 2>, grid, dim3(256), st, a); break;
+    default: launch("batch_prep", wd_prep<128, 2>, grid, dim3(256), st, a); break;
+    }
+}
+
+// Stages in flight, rows and columns per workgroup as measured on the
+// Mistral shape (gate + up / down in us): 32 tokens 45.0 / 25.2 (bx_gate_up64
+// and bx_down 58.0 / 28.8), 64 tokens 55 / 34.6 (85.8 / 42.7), 256 tokens
+// 113 / 67 (four passes of 64: 327 / 168).
+void launch_wide_gate_up(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
+    if (p.parts == 3) launch_wide_gate_moe<64, 3, 128, 1>(p, a, st);
+    else if (p.tok == 128) launch_wide_gate<128, 2, 128, 2>(p, a, st);
+    else if (p.tok == 64) launch_wide_gate<64, 2, 64, 2>(p, a, st);
+    else launch_wide_gate<32, 2, 64, 4>(p, a, st);
+}
+
+void launch_wide_down(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
+    if (p.parts == 3) launch_wide_down_cw<64, 3, 256, 4, 1, 2, wd_down_tiles(64, 3)>(p, a, st);
+    else if (p.tok == 128) launch_wide_down_cw<128, 2, 256, 4, 2, 1, wd_down_tiles(128, 2)>(p, a, st);
+    else if (p.tok == 64) launch_wide_down_cw<64, 2, 128, 4, 2, 1, wd_down_tiles(64, 2)>(p, a, st);
+    else launch_wide_down_cw<32, 2, 128, 8, 2, 1, wd_down_tiles(32, 2)>(p, a, st);
+}
+
+}  // namespace ts

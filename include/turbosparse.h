@@ -110,8 +110,11 @@ size_t ts_ffn_workspace_bytes(int batch, int hidden, int inter, ts_dtype wdtype)
  * read the W_up rows of the union of the tokens' open gates, above that
  * every W_up row is read (nearly all are in the union), and the W_down rows
  * of the union of the active sets; each row once for up to 128 tokens.
- * TS_F32 weights run the single-token kernels per token, and so does a
- * TS_BF16 batch above 64 whose report asks for the union counts.
+ * Batches of TS_F32 weights run batched kernels with fp32 products (row
+ * streams up to 8 tokens, the fp32 matrix operations above) where the
+ * matrices are large enough for that to pay, otherwise the single-token
+ * kernels per token, and so does a TS_BF16 batch above 64 whose report asks
+ * for the union counts.
  */
 ts_status ts_ffn_sparse(const float *x, const void *w_gate, const void *w_up, const void *w_down_t,
                         ts_dtype wdtype, int batch, int hidden, int inter, float *out,
@@ -152,8 +155,9 @@ typedef enum {
  * of G.  TS_ACT_DRELU requires tau == 0 and is ts_ffn_sparse.
  * The activity report gives G_t = {gate > tau} and A_t = {Combined != 0}.
  * Other arguments as ts_ffn_sparse, same workspace size.  TS_ACT_RELU_GATE
- * runs the single-token kernels per token (the batched matrix-core path
- * serves dReLU only).  An unknown `act`, a non-finite tau, or a non-zero tau
+ * with several tokens runs the batched kernels with x and Combined in three
+ * bf16 parts (all 24 bits; TS_F32: fp32) where the matrices are large enough
+ * for that to pay, otherwise the single-token kernels per token.  An unknown `act`, a non-finite tau, or a non-zero tau
  * with TS_ACT_DRELU returns TS_ERR_SHAPE.
  */
 ts_status ts_ffn_sparse_act(const float *x, const void *w_gate, const void *w_up, const void *w_down_t,
@@ -215,9 +219,9 @@ size_t ts_moe_workspace_bytes(int batch, int hidden, int inter, int n_experts, i
  *   topk_w [batch][top_k] fp32 (nullable): their renormalised weights;
  *   stats (nullable): per (token, slot) report, see ts_ffn_stats;
  *   ws / ws_bytes / stream as above.
- * The routing decision never leaves the device.  Batch 1 (and TS_F32
- * weights) run the pipelined single-token kernel, each workgroup computing
- * its token's router; batches with TS_BF16 weights run the matrix-core
+ * The routing decision never leaves the device.  Batch 1 (and small TS_F32
+ * batches) run the pipelined single-token kernel, each workgroup computing
+ * its token's router; other batches run the matrix-core
  * path, each expert's tokens in groups of about twice the expected load (an
  * expert drawing more takes further groups and reads its weights once more
  * per group), above 64 tokens in groups of 64 with x and Combined in three

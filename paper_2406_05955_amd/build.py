@@ -15,7 +15,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libturbosparse.so")
 ARCH = os.environ.get("TS_OFFLOAD_ARCH", "gfx950")
 
-HIP_SOURCES = ["ts_ffn.hip", "ts_batch.hip", "ts_wide.hip", "ts_probe.hip", "ts_runtime.cpp"]
+HIP_SOURCES = ["ts_ffn.hip", "ts_batch.hip", "ts_wide.hip", "ts_rows.hip", "ts_probe.hip", "ts_runtime.cpp"]
 HOST_SOURCES = ["ts_plan.cpp"]
 
 # -packed-fp32-ops: keep the compiler from emitting packed fp32 VALU ops.

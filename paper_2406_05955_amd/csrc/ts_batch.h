@@ -19,6 +19,6 @@ namespace ts {
 ts_status run_batch(const float *x, const void *wg, const void *wu, const void *wd, size_t expert_stride,
                     const int32_t *topk, const float *topw, const BatchPlan &p, float *out,
                     const ts_ffn_stats *stats, int stats_base, void *ws, hipStream_t st, bool dense,
-                    bool xtok = false);
+                    bool xtok = false, int act = 0, float tau = 0.f);
 
 }  // namespace ts

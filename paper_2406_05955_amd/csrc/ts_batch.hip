@@ -67,13 +67,13 @@ struct BxX {
 // holds column lm = (part, slot) as bx_prep lays it out; gathered from the
 // token-major split when the router wrote one (a.xtok), each column at
 // 16 bytes of its token's 32-byte chunk 4 ks + lq (high part first).
-template <int TOK, bool GATHER>
-__device__ __forceinline__ BxX<Bx<TOK>::NX> bx_xsource(const BxArgs &a, int g, int lane, const int *s_tok) {
-    using S = Bx<TOK>;
+template <int TOK, bool GATHER, int M = kBxBf16x2>
+__device__ __forceinline__ BxX<Bx<TOK, M>::NX> bx_xsource(const BxArgs &a, int g, int lane, const int *s_tok) {
+    using S = Bx<TOK, M>;
     constexpr int NX = S::NX;
     const int lm = lane & 15, lq = lane >> 4;
     BxX<NX> xs;
-    xs.frag = reinterpret_cast<const u32x4 *>(a.xhl) + (size_t)g * (a.hpad / 32) * NX * 64;
+    xs.frag = reinterpret_cast<const u32x4 *>(a.xhl) + (size_t)g * (a.hpad * S::ESZ / 64) * NX * 64;
     if constexpr (GATHER) {
         const uint32_t rowb = (uint32_t)a.xchunks * 32u;
         xs.rs = make_rsrc(a.xtok, (uint32_t)a.B * rowb);
@@ -98,19 +98,19 @@ __device__ __forceinline__ BxX<Bx<TOK>::NX> bx_xsource(const BxArgs &a, int g, i
 // of column lm, column = (high or low part, token slot); fragments are 1 KB
 // contiguous, so a wave loads one with a single fully coalesced instruction.
 // Zero past the token count and past H (to hpad).  One thread per (group,
-// k-step, fragment, lane); a block's 256 threads belong to one group (hpad /
-// 32 k-steps per group is a multiple of 32).  Without a routing table (the
-// FFN) the slots are the tokens themselves.  With one (the MoE layer), one
+// k-step, fragment, lane); a block's 256 threads belong to one group (its
+// k-steps are a multiple of 32).  Without a routing table (the FFN) group g
+// holds tokens [g TOK, (g + 1) TOK).  With one (the MoE layer), one
 // wave of each block lists its group's tokens: the (token, rank) pairs are
 // scanned in token-major order, so each expert's list comes out ascending.
 // The group's first block also writes the group tables (token count, and
 // the (group, slot) of each routed pair for the reduce and the report).
-template <int TOK>
+template <int TOK, int M = kBxBf16x2>
 __global__ __launch_bounds__(256) void bx_prep(BxArgs a) {
-    using S = Bx<TOK>;
-    constexpr int NX = S::NX;
+    using S = Bx<TOK, M>;
+    constexpr int NX = S::NX, KE = 64 / S::ESZ, CE = 16 / S::ESZ;  // elements per k-step, per chunk
     __shared__ int s_tok[TOK];
-    const int nks = a.hpad / 32;
+    const int nks = a.hpad / KE;
     const int g = (blockIdx.x * 4) / (NX * nks);
     const bool first = blockIdx.x * 4 == g * NX * nks;
     if (a.topk) {
@@ -118,36 +118,31 @@ __global__ __launch_bounds__(256) void bx_prep(BxArgs a) {
         __syncthreads();
     } else if (blockIdx.x == 0) {
         for (int t = threadIdx.x; t < a.B; t += 256) {
-            a.tslot[t * 2] = 0;
-            a.tslot[t * 2 + 1] = t;
+            a.tslot[t * 2] = t / TOK;
+            a.tslot[t * 2 + 1] = t % TOK;
         }
-        if (threadIdx.x == 0) a.gcount[0] = a.B;
+        for (int q = threadIdx.x; q < a.G; q += 256) a.gcount[q] = min(TOK, a.B - q * TOK);
     }
     const int idx = blockIdx.x * 256 + threadIdx.x;
     if (idx >= a.G * nks * NX * 64) return;
     const int lane = idx & 63, lm = lane & 15, lq = lane >> 4;
     const int f = (idx >> 6) % NX;
     const int ks = (idx >> 6) / NX % nks;
-    const int hl = S::PACK ? (lm >> 3) : (f & 1);
-    const int slot = S::PACK ? (lm & 7) : 16 * (f >> 1) + lm;
-    const int t = a.topk ? s_tok[slot] : (slot < a.B ? slot : -1);
-    const int k0 = ks * 32 + 8 * lq;
-    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (t >= 0 && k0 < a.H) {  // H is a multiple of 8, so all 8 are in range
-        const f32x4 *src = reinterpret_cast<const f32x4 *>(a.x + (size_t)t * a.H + k0);
-        const f32x4 p = src[0], q = src[1];
-        v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w;
-        v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
-    }
-    uint32_t o[4];
+    const int part = S::PACK ? 2 * f + (lm >> 3) : f % S::P;
+    const int slot = S::PACK ? (lm & 7) : 16 * (f / S::P) + lm;
+    const int t = a.topk ? s_tok[slot] : (g * TOK + slot < a.B ? g * TOK + slot : -1);
+    const int k0 = ks * KE + CE * lq;
+    const bool in = t >= 0 && k0 < a.H && part < S::P;  // H is a multiple of CE, so the whole chunk is in range
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(a.x + (in ? (size_t)t * a.H + k0 : 0));
+    f32x4 p = in ? src[0] : f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 o = __builtin_bit_cast(u32x4, p);
+    if constexpr (!S::F32) {
+        const f32x4 q = in ? src[1] : f32x4{0.f, 0.f, 0.f, 0.f};
+        const float v[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        uint32_t h0, l0, h1, l1;
-        split_hi_lo(v[2 * e], h0, l0);
-        split_hi_lo(v[2 * e + 1], h1, l1);
-        o[e] = hl ? (l0 | (l1 << 16)) : (h0 | (h1 << 16));
+        for (int e = 0; e < 4; ++e) o[e] = bf16_sel<S::P>(v[2 * e], part) | (bf16_sel<S::P>(v[2 * e + 1], part) << 16);
     }
-    reinterpret_cast<u32x4 *>(a.xhl)[idx] = u32x4{o[0], o[1], o[2], o[3]};
+    reinterpret_cast<u32x4 *>(a.xhl)[idx] = o;
 }
 
 // ---------------------------------------------------------------------------
@@ -169,23 +164,28 @@ __device__ __forceinline__ int bx_swz(int r, int c) {
     return KS == 4 ? (c ^ (r & 15)) : (c ^ ((r >> 1) & 7));
 }
 
-template <int TOK, int MT, int KS, int D, bool GATHER = false>
-__device__ __forceinline__ void bx_kloop(const char *wbase, const uint32_t (&roff)[MT * KS], int H,
-                                         const BxX<Bx<TOK>::NX> &xs, int ks0, int nbat, int lane, u32x4 *sw,
-                                         f32x4 (&acc)[MT][Bx<TOK>::NT]) {
-    using S = Bx<TOK>;
-    constexpr int NX = S::NX, CPR = 4 * KS, RPI = 16 / KS, NI = MT * KS;
+// (k-steps and offsets in bytes of a row, Hb = its length.)  The fp32 and
+// three-part modes, whose other route is the single-token kernels' short fp32
+// chains, sum each batch from zero and add it to the accumulators (FOLD): a
+// chain of roundings spans one batch, not the wave's quarter.
+template <int TOK, int MT, int KS, int D, bool GATHER = false, int M = kBxBf16x2>
+__device__ __forceinline__ void bx_kloop(const char *wbase, const uint32_t (&roff)[MT * KS], int Hb,
+                                         const BxX<Bx<TOK, M>::NX> &xs, int ks0, int nbat, int lane, u32x4 *sw,
+                                         f32x4 (&acc)[MT][Bx<TOK, M>::NT]) {
+    using S = Bx<TOK, M>;
+    constexpr int NX = S::NX, NT = S::NT, CPR = 4 * KS, RPI = 16 / KS, NI = MT * KS;
+    constexpr bool FOLD = M != kBxBf16x2;
+    static_assert(!GATHER || M == kBxBf16x2, "the router's split has two parts here");
     // each wave's k-steps (hpad / 128, hpad a multiple of kBxKQuant) come in
     // batches of KS; the ring below needs their count to be a multiple of D
     static_assert((kBxKQuant / 128 / KS) % D == 0, "k-step batches per wave must be a multiple of D");
     const int lm = lane & 15, lq = lane >> 4;
     const int lc = lane % CPR, lr = lane / CPR;
     u32x4 w[D][NI], xv[D][NX][KS];
-    // weights: uniform base + 32-bit per-lane byte offset (row * H * 2 + k * 2)
+    // weights: uniform base + 32-bit per-lane byte offset (row * Hb + k bytes)
     auto issue = [&](int d, int b) {
-        const int kb = (ks0 + b * KS) * 32;
-        const int k = kb + 8 * lc;
-        const uint32_t kw = 2u * (uint32_t)(k < H ? k : H - 8);
+        const int kb = (ks0 + b * KS) * 64 + 16 * lc;
+        const uint32_t kw = (uint32_t)(kb < Hb ? kb : Hb - 16);
 #pragma unroll
         for (int j = 0; j < NI; ++j) w[d][j] = ld_stream(wbase + (roff[j] + kw));
         if constexpr (GATHER) {
@@ -219,15 +219,37 @@ __device__ __forceinline__ void bx_kloop(const char *wbase, const uint32_t (&rof
                 const int r = 16 * mt + lm;
                 av[mt][s] = sw[r * CPR + bx_swz<KS>(r, 4 * s + lq)];
             }
+        if constexpr (FOLD) {
+            f32x4 part[MT][NT];
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int f = 0; f < NX; ++f)
+                for (int nt = 0; nt < NT; ++nt) part[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    f32x4 &c = acc[mt][S::PACK ? 0 : f >> 1];
-                    c = mfma_bf16(av[mt][s], xv[d][f][s], c);
-                }
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int f = 0; f < NX; ++f)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        f32x4 &c = part[mt][S::PACK ? 0 : f / S::P];
+                        if constexpr (S::F32) c += bx_mma<M>(av[mt][s], xv[d][f][s], f32x4{0.f, 0.f, 0.f, 0.f});
+                        else c = bx_mma<M>(av[mt][s], xv[d][f][s], c);
+                    }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += part[mt][nt];
+        } else {
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int f = 0; f < NX; ++f)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        f32x4 &c = acc[mt][S::PACK ? 0 : f >> 1];
+                        c = mfma_bf16(av[mt][s], xv[d][f][s], c);
+                    }
+        }
         __builtin_amdgcn_wave_barrier();
     };
     // nbat is a positive multiple of D (hpad is a multiple of 4 waves x 32 x
@@ -274,8 +296,8 @@ __device__ __forceinline__ void bx_combine(f32x4 (&acc)[2][NT], f32x4 (*s_red)[2
 // With packed fragments, column lm holds the high-part sum of token lm & 7
 // (lm < 8) or its low-part sum (lm >= 8): add the partner column, so both
 // lanes of a pair end with the same total.
-template <int TOK>
-__device__ __forceinline__ void bx_pair_sum(f32x4 (&acc)[2][Bx<TOK>::NT]) {
+template <int TOK, int NT>
+__device__ __forceinline__ void bx_pair_sum(f32x4 (&acc)[2][NT]) {
     if (!Bx<TOK>::PACK) return;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
@@ -321,14 +343,14 @@ __device__ __forceinline__ void bx_token_masks(const bool (&pred)[2][NT][4], con
     }
 }
 
-template <int TOK, int KS, int D, bool GATHER = false>
+template <int TOK, int KS, int D, bool GATHER = false, int M = kBxBf16x2>
 __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up(BxArgs a) {
-    using S = Bx<TOK>;
+    using S = Bx<TOK, M>;
     constexpr int NT = S::NT, NX = S::NX;
     constexpr int CPR = 4 * KS, RPI = 16 / KS;
-    __shared__ f32x4 s_red[4][2][NT][64];
     __shared__ float s_g[kBxRows][TOK];
-    __shared__ __attribute__((aligned(16))) uint16_t s_h[kBxRows][2 * TOK];
+    __shared__ __attribute__((aligned(16))) uint8_t s_h[kBxRows][S::REC];
+    __shared__ f32x4 s_red[4][2][NT][64];
     __shared__ u32x4 s_stage[4][kBxRows * CPR];  // per-wave weight staging
     __shared__ int s_tok[GATHER ? TOK : 1];
     __shared__ int s_ng;
@@ -363,14 +385,16 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up(BxArgs a) {
             }
         return;
     }
-    for (int e = tid; e < 2 * TOK * kBxRows / 8; e += 256)
+    for (int e = tid; e < S::REC * kBxRows / 16; e += 256)
         reinterpret_cast<u32x4 *>(&s_h[0][0])[e] = u32x4{0u, 0u, 0u, 0u};
 
     const int r0 = tile * kBxRows;
-    const uint16_t *wg = reinterpret_cast<const uint16_t *>(a.wg) + (size_t)(g / a.vpe) * a.expert_stride;
-    const uint16_t *wu = reinterpret_cast<const uint16_t *>(a.wu) + (size_t)(g / a.vpe) * a.expert_stride;
-    const int nks = a.hpad / 32;
-    const BxX<NX> xs = bx_xsource<TOK, GATHER>(a, g, lane, s_tok);
+    const size_t eoff = (size_t)(g / a.vpe) * a.expert_stride * S::ESZ;
+    const char *wg = static_cast<const char *>(a.wg) + eoff;
+    const char *wu = static_cast<const char *>(a.wu) + eoff;
+    const int Hb = a.H * S::ESZ;  // row length in bytes
+    const int nks = a.hpad * S::ESZ / 64;
+    const BxX<NX> xs = bx_xsource<TOK, GATHER, M>(a, g, lane, s_tok);
     const int kpw = nks / 4;  // k-steps per wave
     const int ks0 = wave * kpw, nbat = kpw / KS;
     u32x4 *sw = s_stage[wave];
@@ -387,12 +411,16 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up(BxArgs a) {
     {
         uint32_t roff[2 * KS];
 #pragma unroll
-        for (int j = 0; j < 2 * KS; ++j) roff[j] = 2u * (uint32_t)min(r0 + RPI * j + lr, a.I - 1) * (uint32_t)a.H;
-        bx_kloop<TOK, 2, KS, D, GATHER>(reinterpret_cast<const char *>(wg), roff, a.H, xs, ks0, nbat, lane, sw, acc);
+        for (int j = 0; j < 2 * KS; ++j) roff[j] = (uint32_t)min(r0 + RPI * j + lr, a.I - 1) * (uint32_t)Hb;
+        bx_kloop<TOK, 2, KS, D, GATHER, M>(wg, roff, Hb, xs, ks0, nbat, lane, sw, acc);
     }
     bx_combine<NT>(acc, s_red, wave, lane);
     bx_pair_sum<TOK>(acc);
 
+    // (two-part operands serve dReLU only; an empty slot's gate is 0 there)
+    const int act_fn = M == kBxBf16x2 ? 0 : a.act;
+    const float thr = gate_threshold(act_fn, a.tau);
+    auto held = [&](int nt) { return (S::PACK ? lm & 7 : 16 * nt + lm) < ng; };
     bool open[2][NT][4];
     int rowbit[2][4];
 #pragma unroll
@@ -403,7 +431,8 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up(BxArgs a) {
             rowbit[mt][i] = r;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                open[mt][nt][i] = r0 + r < a.I && (a.dense || acc[mt][nt][i] > 0.f);
+                if constexpr (M == kBxBf16x2) open[mt][nt][i] = r0 + r < a.I && (a.dense || acc[mt][nt][i] > 0.f);
+                else open[mt][nt][i] = r0 + r < a.I && (a.dense || (acc[mt][nt][i] > thr && held(nt)));
                 if (wave == 0 && tok_lane) s_g[r][S::PACK ? lm : 16 * nt + lm] = acc[mt][nt][i];
             }
         }
@@ -429,20 +458,20 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up(BxArgs a) {
 #pragma unroll
         for (int j = 0; j < 2 * KS; ++j) {
             const int u = RPI * j + lr;
-            roff[j] = 2u * (uint32_t)(r0 + nth_set_bit(umask, u < nu ? u : 0)) * (uint32_t)a.H;
+            roff[j] = (uint32_t)(r0 + nth_set_bit(umask, u < nu ? u : 0)) * (uint32_t)Hb;
         }
-        bx_kloop<TOK, 2, KS, D, GATHER>(reinterpret_cast<const char *>(wu), roff, a.H, xs, ks0, nbat, lane, sw, uacc);
+        bx_kloop<TOK, 2, KS, D, GATHER, M>(wu, roff, Hb, xs, ks0, nbat, lane, sw, uacc);
     } else if (nu > 0) {
         uint32_t roff[KS];
 #pragma unroll
         for (int j = 0; j < KS; ++j) {
             const int u = RPI * j + lr;
-            roff[j] = 2u * (uint32_t)(r0 + nth_set_bit(umask, u < nu ? u : 0)) * (uint32_t)a.H;
+            roff[j] = (uint32_t)(r0 + nth_set_bit(umask, u < nu ? u : 0)) * (uint32_t)Hb;
         }
         f32x4 u1[1][NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) u1[0][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        bx_kloop<TOK, 1, KS, D, GATHER>(reinterpret_cast<const char *>(wu), roff, a.H, xs, ks0, nbat, lane, sw, u1);
+        bx_kloop<TOK, 1, KS, D, GATHER, M>(wu, roff, Hb, xs, ks0, nbat, lane, sw, u1);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) uacc[0][nt] = u1[0][nt];
     }
@@ -464,9 +493,10 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up(BxArgs a) {
             for (int nt = 0; nt < NT; ++nt) {
                 const float gv = s_g[r][S::PACK ? (lm & 7) : 16 * nt + lm];
                 const float uv = uacc[mt][nt][i];
-                const bool on = j < nu && gv > 0.f && uv > 0.f;
+                bool on = j < nu && gv > thr && combined_nonzero(act_fn, uv);
+                if constexpr (M != kBxBf16x2) on = on && held(nt);
                 act[mt][nt][i] = on || (a.dense && j < nu);
-                hv[mt][nt][i] = on ? gv * uv : 0.f;
+                hv[mt][nt][i] = on ? combined_value(act_fn, a.tau, gv, uv) : 0.f;
             }
         }
     const uint32_t amask_u = bx_any_rows<NT>(act);  // over union indices
@@ -490,17 +520,20 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up(BxArgs a) {
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) {
                         const int t = S::PACK ? lm : 16 * nt + lm;
-                        uint32_t hi, lo;
-                        split_hi_lo(hv[mt][nt][i], hi, lo);
-                        s_h[slot][t] = (uint16_t)hi;
-                        s_h[slot][TOK + t] = (uint16_t)lo;
+                        if constexpr (S::F32) {
+                            reinterpret_cast<float *>(s_h[slot])[t] = hv[mt][nt][i];
+                        } else {
+#pragma unroll
+                            for (int p = 0; p < S::P; ++p)
+                                reinterpret_cast<uint16_t *>(s_h[slot])[p * TOK + t] = (uint16_t)bf16_part(hv[mt][nt][i], p);
+                        }
                     }
                 }
             }
     }
     __syncthreads();  // s_h complete
-    u32x4 *hdst = reinterpret_cast<u32x4 *>(a.hfrag + tix * (2 * TOK * kBxRows));
-    for (int e = tid; e < 2 * TOK * kBxRows / 8; e += 256) hdst[e] = reinterpret_cast<const u32x4 *>(&s_h[0][0])[e];
+    u32x4 *hdst = reinterpret_cast<u32x4 *>(a.hfrag) + tix * (S::REC * kBxRows / 16);
+    for (int e = tid; e < S::REC * kBxRows / 16; e += 256) hdst[e] = reinterpret_cast<const u32x4 *>(&s_h[0][0])[e];
     if (wave == 0) {
         if (lane < kBxRows) {  // an empty tile lists row 0 (always < I), never used
             const int j = nth_set_bit(amask_u, lane < na ? lane : 0);
@@ -662,7 +695,7 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up64(BxArgs a)
         uint32_t roff[4 * KS];
 #pragma unroll
         for (int j = 0; j < 4 * KS; ++j) roff[j] = 2u * (uint32_t)min(r0 + RPI * j + lr, a.I - 1) * (uint32_t)a.H;
-        bx_kloop<TOK, 4, KS, D, GATHER>(reinterpret_cast<const char *>(wg), roff, a.H, xs, ks0, nbat, lane, sw, acc);
+        bx_kloop<TOK, 4, KS, D, GATHER>(reinterpret_cast<const char *>(wg), roff, 2 * a.H, xs, ks0, nbat, lane, sw, acc);
     }
     bx_combine_mt<4, NT>(acc, s_red, wave, lane);
 
@@ -712,7 +745,7 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up64(BxArgs a)
         for (int mt = 0; mt < MU; ++mt)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) ua[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        bx_kloop<TOK, MU, KS, D, GATHER>(reinterpret_cast<const char *>(wu), roff, a.H, xs, ks0, nbat, lane, sw, ua);
+        bx_kloop<TOK, MU, KS, D, GATHER>(reinterpret_cast<const char *>(wu), roff, 2 * a.H, xs, ks0, nbat, lane, sw, ua);
 #pragma unroll
         for (int mt = 0; mt < MU; ++mt)
 #pragma unroll
@@ -820,14 +853,16 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up64(BxArgs a)
 // row load zeros (out-of-range buffer offset) with zero Combined.  Loads of the next DD - 1
 // blocks are in flight while a block is contracted; the four waves' sums
 // are added in a fixed order at the end.
-template <int TOK, int DD>
+template <int TOK, int DD, int M = kBxBf16x2>
 __global__ __launch_bounds__(256, TOK <= 16 ? 2 : 1) void bx_down(BxArgs a) {
-    using S = Bx<TOK>;
-    constexpr int NT = S::NT, NX = S::NX;
+    using S = Bx<TOK, M>;
+    constexpr int NT = S::NT, NX = S::NX, P = S::P;
+    constexpr int AR = S::PACK ? 16 * NX : P * TOK;  // rows of the Combined tile (packed: an unused part is zero)
     constexpr int REG = 512 * NT;  // 16-byte units per wave: 8 KB staging, or its 8 x NT accumulators
     constexpr int BG = 2;          // n-tiles whose operands are read from LDS together
     constexpr int AP = 40;         // bf16 per row of the Combined tile (80 bytes: 16-row reads do not conflict)
-    constexpr int HC = TOK / 8;    // 16-byte Combined chunks per lane (token half of one slot)
+    constexpr int RCH = P * TOK / 8;         // 16-byte chunks of a Combined record
+    constexpr int HC = (AR / 8 + 1) / 2;     // chunks per lane: hh, hh + 2, ... of its slot
     constexpr int MAXT = bx_down_tiles(TOK);  // tiles per chunk at most
     constexpr int MAXR = MAXT * kBxRows;       // list entries at most
     constexpr int WPT = MAXR / 4 / 256;        // row-byte words (4 rows each) per thread
@@ -839,7 +874,7 @@ __global__ __launch_bounds__(256, TOK <= 16 ? 2 : 1) void bx_down(BxArgs a) {
     __shared__ int s_wsum[4];
     // the Combined tile: past the staging 8 KB of the wave's region when it has room (NT >= 2)
     constexpr bool AIN = NT >= 2;
-    __shared__ __attribute__((aligned(16))) uint16_t s_a_own[AIN ? 1 : 4][2 * TOK][AP];
+    __shared__ __attribute__((aligned(16))) uint16_t s_a_own[AIN ? 1 : 4][AR][AP];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lm = lane & 15, lq = lane >> 4;
@@ -960,9 +995,12 @@ __global__ __launch_bounds__(256, TOK <= 16 ? 2 : 1) void bx_down(BxArgs a) {
             const uint32_t he = s_ent[bb * kBxRows + hj];
             hok[d] = he != kPadRow;
             const size_t hx = hok[d] ? (tbase + (he >> 10)) * kBxRows + ((he >> 5) & 31u) : 0;
-            const uint16_t *hs = a.hfrag + hx * (2 * TOK) + hh * TOK;
+            const uint16_t *hs = a.hfrag + hx * (P * TOK);
 #pragma unroll
-            for (int c = 0; c < HC; ++c) hq[d][c] = ld_cached(hs + 8 * c);
+            for (int c = 0; c < HC; ++c) {
+                const int q = hh + 2 * c;  // (AR and P * TOK may differ by one chunk: re-read, written as zero)
+                hq[d][c] = ld_cached(hs + 8 * (AR / 8 == RCH || q < RCH ? q : 0));
+            }
         };
         auto mma = [&](int d) {
 #pragma unroll
@@ -973,14 +1011,14 @@ __global__ __launch_bounds__(256, TOK <= 16 ? 2 : 1) void bx_down(BxArgs a) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const uint16_t v = (uint16_t)(e & 1 ? w4[e >> 1] >> 16 : w4[e >> 1] & 0xFFFFu);
-                    s_a[hh * TOK + 8 * c + e][hj] = hok[d] ? v : (uint16_t)0;
+                    s_a[8 * (hh + 2 * c) + e][hj] = hok[d] && (AR / 8 == RCH || hh + 2 * c < RCH) ? v : (uint16_t)0;
                 }
             }
             __builtin_amdgcn_wave_barrier();
             u32x4 af[NX];
 #pragma unroll
             for (int f = 0; f < NX; ++f) {
-                const int ar = S::PACK ? lm : (f & 1) * TOK + 16 * (f >> 1) + lm;
+                const int ar = S::PACK ? 16 * f + lm : (f % P) * TOK + 16 * (f / P) + lm;
                 af[f] = *reinterpret_cast<const u32x4 *>(&s_a[ar][8 * lq]);
             }
 #pragma unroll
@@ -998,7 +1036,7 @@ __global__ __launch_bounds__(256, TOK <= 16 ? 2 : 1) void bx_down(BxArgs a) {
                     const u32x4 b = __builtin_bit_cast(u32x4, bfr[u]);
 #pragma unroll
                     for (int f = 0; f < NX; ++f) {
-                        f32x4 &c = acc[n2 + u][S::PACK ? 0 : f >> 1];
+                        f32x4 &c = acc[n2 + u][S::PACK ? 0 : f / P];
                         c = mfma_bf16(af[f], b, c);
                     }
                 }
@@ -1057,6 +1095,124 @@ __global__ __launch_bounds__(256, TOK <= 16 ? 2 : 1) void bx_down(BxArgs a) {
                 const bool ok = (S::PACK ? lq < 2 : true) && tok < ng && col < H;
                 if (ok) a.partial[(((size_t)g * TOK + tok) * a.nchunks + chunk) * H + col] = v[i];
             }
+        }
+    }
+}
+
+// Down with fp32 weights: workgroup (group, chunk of tiles, 128-column
+// slice), 4 waves that take the chunk's 32-row blocks in turn.  A 16-byte
+// load of four rows x 64 columns (lane (lm, lq): listed row 4 s + lq, columns
+// 4 lm .. 4 lm + 3) is four fp32 matrix operands as it stands (register j:
+// the 16 columns 4 lm + j, contraction over the four rows), so nothing goes
+// through LDS; each lane's Combined value of (slot, token) is one 4-byte
+// load.  A block's products are summed from zero and added to the wave's
+// sums (short chains of roundings); the four waves' sums are added in a
+// fixed order.
+template <int TOK>
+__global__ __launch_bounds__(256, 2) void bx_down_f32(BxArgs a) {
+    constexpr int NT = TOK / 16, MAXT = bx_down_tiles(TOK);
+    constexpr int NU = kBxSliceCols / 64, NS = kBxRows / 4;  // 64-column loads per row group, row groups per block
+    __shared__ f32x4 s_sum[4][NU * 4 * NT][64];
+    __shared__ uint32_t s_ent[MAXT * kBxRows];
+    __shared__ int s_pre[MAXT + 1];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lm = lane & 15, lq = lane >> 4;
+    const int slice = blockIdx.x % a.nslices, pair = blockIdx.x / a.nslices;
+    const int chunk = pair % a.nchunks;
+    const int g = bx_group_at(pair / a.nchunks, a.G, a.vpe);
+    const int ng = a.gcount[g];
+    if (ng == 0) return;
+    const int H = a.H, t0 = chunk * a.tpc, ntc = min(a.tpc, a.ntiles - t0);
+    const size_t tbase = (size_t)g * a.ntiles + t0;
+    const int nblk = bx_list_rows<256, kBxRows>(a, tbase, ntc, s_pre, s_ent);
+
+    const char *wd = static_cast<const char *>(a.wd) + (size_t)(g / a.vpe) * a.expert_stride * 4;
+    const __amdgpu_buffer_rsrc_t rwd = make_rsrc(wd, (uint32_t)a.I * (uint32_t)H * 4u);
+    const __amdgpu_buffer_rsrc_t rh = make_rsrc(reinterpret_cast<const float *>(a.hfrag) + tbase * (kBxRows * TOK),
+                                                (uint32_t)ntc * (kBxRows * TOK * 4u));
+    const int col0 = slice * kBxSliceCols + 4 * lm;
+
+    f32x4 acc[NU][4][NT];
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[u][j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr uint32_t kOob = 0xFFFFFFF0u;  // past any matrix here: zeros, no traffic
+    u32x4 wv[2][NS][NU];
+    float hv[2][NS][NT];
+    auto issue = [&](int d, int b) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const uint32_t e = b < nblk ? s_ent[b * kBxRows + 4 * s + lq] : kPadRow;
+            const uint32_t n = (uint32_t)(t0 + (int)(e >> 10)) * kBxRows + (e & 31u);
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const int c = col0 + 64 * u;
+                wv[d][s][u] = ld_buf_stream(rwd, e != kPadRow && c < H ? (n * (uint32_t)H + (uint32_t)c) * 4u : kOob);
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                hv[d][s][nt] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(
+                               rh, e != kPadRow ? ((e >> 5) * TOK + 16 * nt + lm) * 4u : kOob, 0, 0));
+        }
+    };
+    auto block = [&](int d) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                f32x4 c[2][4];  // the block's halves
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) c[h][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int s = h * NS / 2; s < (h + 1) * NS / 2; ++s) {
+                        const f32x4 w = __builtin_bit_cast(f32x4, wv[d][s][u]);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            c[h][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j], hv[d][s][nt], c[h][j], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[u][j][nt] += c[0][j] + c[1][j];
+            }
+    };
+    issue(0, wave);
+    issue(1, wave + 4);
+    for (int b = wave; b < nblk; b += 8) {
+        block(0);
+        issue(0, b + 8);
+        if (b + 4 < nblk) block(1);
+        issue(1, b + 12);
+    }
+    // lane (lm, lq), register i of tile (u, j): column 64 u + 4 (4 lq + i) + j, token 16 nt + lm
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) s_sum[wave][(u * 4 + j) * NT + nt][lane] = acc[u][j][nt];
+    __syncthreads();
+    for (int p = wave; p < NU * NT; p += 4) {
+        const int u = p / NT, nt = p % NT;
+        f32x4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = (u * 4 + j) * NT + nt;
+            v[j] = (s_sum[0][e][lane] + s_sum[1][e][lane]) + (s_sum[2][e][lane] + s_sum[3][e][lane]);
+        }
+        const int t = 16 * nt + lm;
+        float *prow = a.partial + (((size_t)g * TOK + t) * a.nchunks + chunk) * H;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int col = slice * kBxSliceCols + 64 * u + 4 * (4 * lq + i);
+            if (t < ng && col < H)
+                *reinterpret_cast<f32x4 *>(prow + col) = f32x4{v[0][i], v[1][i], v[2][i], v[3][i]};
         }
     }
 }
@@ -1228,6 +1384,22 @@ void launch_tok(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     launch("batch_down", bx_down<TOK, Bx<TOK>::DD>, grid, dim3(256), st, a);
 }
 
+// The fp32-exact modes (kBxBf16x3, kBxF32).
+template <int TOK, int KS, int M>
+void launch_exact(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
+    using S = Bx<TOK, M>;
+    if (p.rows) {  // fp32, a few tokens: no fragments needed
+        launch_rows(p, a, st);
+    } else {
+        const int nthreads = p.groups * (p.hpad * S::ESZ / 64) * S::NX * 64;
+        launch("batch_prep", bx_prep<TOK, M>, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), st, a);
+        launch("batch_gate_up", bx_gate_up<TOK, KS, 2, false, M>, dim3((unsigned)(p.groups * p.ntiles)), dim3(256), st, a);
+    }
+    const dim3 grid((unsigned)(p.groups * p.nchunks * p.nslices));
+    if constexpr (S::F32) launch("batch_down", bx_down_f32<TOK>, grid, dim3(256), st, a);
+    else launch("batch_down", bx_down<TOK, 2, M>, grid, dim3(256), st, a);
+}
+
 }  // namespace
 
 // One pass of the batched path for up to kBxMaxTokens tokens.  x and out are
@@ -1235,7 +1407,8 @@ void launch_tok(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
 // pass's tokens.  Stats arrays are indexed from stats_base.
 ts_status run_batch(const float *x, const void *wg, const void *wu, const void *wd, size_t expert_stride,
                     const int32_t *topk, const float *topw, const BatchPlan &p, float *out,
-                    const ts_ffn_stats *stats, int stats_base, void *ws, hipStream_t st, bool dense, bool xtok) {
+                    const ts_ffn_stats *stats, int stats_base, void *ws, hipStream_t st, bool dense, bool xtok,
+                    int act, float tau) {
     BxArgs a;
     a.dense = dense ? 1 : 0;
     a.x = x;
@@ -1273,15 +1446,21 @@ ts_status run_batch(const float *x, const void *wg, const void *wu, const void *
     const bool want_lists = stats && (stats->n_gate || stats->n_active || stats->gate_idx || stats->active_idx);
     a.want_masks = want_lists ? 1 : 0;
 
-    a.act = 0;
-    a.tau = 0.f;
+    a.act = act;
+    a.tau = tau;
     if (p.wide) {
         if (!a.topk) launch_wide_prep(p, a, st);
         // (the "bx_gate" knob compares the one-pass kernels' gate + up: same operands, same bits)
-        if (tuned("bx_gate") == 0 || p.tok > 64 || a.topk) launch_wide_gate_up(p, a, st);
+        if (tuned("bx_gate") == 0 || p.tok > 64 || p.parts == 3) launch_wide_gate_up(p, a, st);
         else if (p.tok == 64) launch_gate_up<64>(p, a, st);
         else launch_gate_up<32>(p, a, st);
         launch_wide_down(p, a, st);
+    } else if (p.mode == kBxF32) {
+        if (p.tok == 16) launch_exact<16, 4, kBxF32>(p, a, st);
+        else launch_exact<32, 2, kBxF32>(p, a, st);
+    } else if (p.mode == kBxBf16x3) {
+        if (p.tok == 8) launch_exact<8, 2, kBxBf16x3>(p, a, st);
+        else launch_exact<16, 2, kBxBf16x3>(p, a, st);
     } else switch (p.tok) {
     case 8: launch_tok<8>(p, a, st); break;
     case 16: launch_tok<16>(p, a, st); break;

@@ -19,18 +19,59 @@ __device__ __forceinline__ f32x4 mfma_bf16(const u32x4 a, const u32x4 b, const f
                                                    0, 0, 0);
 }
 
-// Shape constants per token-slot count TOK (8, 16, 32, 64).
-template <int TOK>
+// Shape constants per token-slot count TOK (8, 16, 32, 64).  A k-step is 64
+// bytes of a weight row (32 bf16 or 16 fp32 elements): one 16-byte chunk per
+// lane of a 16-row operand in every mode.
+template <int TOK, int M = kBxBf16x2>
 struct Bx {
-    static constexpr bool PACK = TOK == 8;          // high and low parts share one 16-column tile
-    static constexpr int NT = PACK ? 1 : TOK / 16;  // 16-token accumulator tiles
-    static constexpr int NX = PACK ? 1 : 2 * NT;    // operand fragments per 32-wide k-step (x or Combined)
+    static constexpr bool F32 = M == kBxF32;
+    static constexpr int ESZ = F32 ? 4 : 2;              // bytes per weight element
+    static constexpr int P = F32 ? 1 : (M == kBxBf16x3 ? 3 : 2);
+    static constexpr bool PACK = TOK == 8;               // two parts share one 16-column tile
+    static_assert(!(PACK && F32), "fp32 operands: 16 or more token slots");
+    static constexpr int NT = PACK ? 1 : TOK / 16;       // 16-token accumulator tiles
+    static constexpr int NX = PACK ? (P + 1) / 2 : P * NT;  // operand fragments per k-step (x or Combined)
+    static constexpr int REC = F32 ? TOK * 4 : P * TOK * 2; // bytes of a slot's Combined record
     // k-steps per batch of gate / up loads (default; measured: 2 at 8 token
     // slots, 4 at 16, 2 past that, where deeper rings spill)
     static constexpr int KS = PACK ? 2 : (NX <= 2 ? 4 : 2);
     static constexpr int D = 2;                     // gate / up batches in flight per wave (default)
     static constexpr int DD = 2;                    // down blocks in flight per wave (default)
 };
+
+// One k-step's product of a 16-row weight operand with a 16-column x operand
+// (fp32: the lane's four elements in four steps; the k order inside a k-step
+// is the same for both operands).
+template <int M>
+__device__ __forceinline__ f32x4 bx_mma(const u32x4 a, const u32x4 b, f32x4 c) {
+    if constexpr (M == kBxF32) {
+        const f32x4 af = __builtin_bit_cast(f32x4, a), bf = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c = __builtin_amdgcn_mfma_f32_16x16x4f32(af[j], bf[j], c, 0, 0, 0);
+        return c;
+    } else {
+        return mfma_bf16(a, b, c);
+    }
+}
+
+// Part p (< P, run-time) of v, without a branch.
+template <int P>
+__device__ __forceinline__ uint32_t bf16_sel(float v, int p) {
+    uint32_t out = 0;
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        const uint32_t b = bf16_bits(v);
+        out = q == p ? b : out;
+        v -= __uint_as_float(b << 16);  // exact
+    }
+    return out;
+}
+
+// Part p of v: the bf16 rounding of what the earlier parts leave.
+__device__ __forceinline__ uint32_t bf16_part(float v, int p) {
+    for (int q = 0; q < p; ++q) v -= __uint_as_float(bf16_bits(v) << 16);  // exact
+    return bf16_bits(v);
+}
 
 struct BxArgs {
     const float *x;          // [tokens][H] (already offset to the pass's first token)
@@ -60,6 +101,9 @@ struct BxArgs {
 };
 
 constexpr uint32_t kPadRow = 0xFFFFFFFFu;  // row-list padding of the down kernels
+
+// Gate + up of a few tokens with fp32 weights by row streams (ts_rows.hip).
+void launch_rows(const BatchPlan &p, const BxArgs &a, hipStream_t st);
 
 // The wide kernels (ts_wide.hip) of one call: x fragments and group tables
 // (without a routing table), gate + up, down.
@@ -96,6 +140,42 @@ __device__ __forceinline__ int bx_list_group(const BxArgs &a, int g, int lane, i
     for (int sl = n + lane; sl < TOK; sl += 64) s_tok[sl] = -1;
     if (tables && lane == 0) a.gcount[g] = n;
     return n;
+}
+
+// A down workgroup's row list: the active rows of `ntc` tiles from tile
+// index tbase, tile after tile, as (tile within the chunk) << 10 | slot << 5
+// | row, padded with kPadRow to whole blocks of KB rows; s_pre (ntc + 1) is
+// scratch.  Returns the number of blocks; ends with a barrier.
+template <int THREADS, int KB>
+__device__ __forceinline__ int bx_list_rows(const BxArgs &a, size_t tbase, int ntc, int *s_pre, uint32_t *s_ent) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid < 64) {  // wave 0 scans the tiles' active counts
+        int base = 0;
+        for (int t = 0; t < ntc; t += 64) {
+            const int v = t + lane < ntc ? a.cnt[(tbase + t + lane) * 2 + 1] : 0;
+            int inc = v;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int u = __shfl_up(inc, o, 64);
+                if (lane >= o) inc += u;
+            }
+            if (t + lane < ntc) s_pre[t + lane] = base + inc - v;
+            base += __shfl(inc, 63, 64);
+        }
+        if (lane == 0) s_pre[ntc] = base;
+    }
+    __syncthreads();
+    const int total = s_pre[ntc];
+    const int nblk = (total + KB - 1) / KB;
+    for (int e = tid; e < ntc * kBxRows; e += THREADS) {
+        const int t = e / kBxRows, s = e % kBxRows;
+        const int base = s_pre[t];
+        if (s < s_pre[t + 1] - base)
+            s_ent[base + s] = ((uint32_t)t << 10) | ((uint32_t)s << 5) | (uint32_t)(a.arow[tbase * kBxRows + e] & 31);
+    }
+    for (int e = total + tid; e < nblk * KB; e += THREADS) s_ent[e] = kPadRow;
+    __syncthreads();
+    return nblk;
 }
 
 // Position of the n-th (from 0) set bit of m, by halving with population

@@ -2285,6 +2285,14 @@ ts_status check_ffn_args(const float *x, const void *wg, const void *wu, const v
     return TS_OK;
 }
 
+// The fp32-exact batched kernels for an FFN call whose other route is the
+// single-token kernels (the union counts need a single group).
+bool plan_exact_ffn(int batch, int hidden, int inter, ts_dtype dt, const ts_ffn_stats *stats, BatchPlan *bp) {
+    return tuned("batch_path") == 0 && tuned("ffn_path") == 0 && exact_pays(batch, hidden, inter, 1, 1, dt) &&
+           plan_exact(batch, hidden, inter, 1, 1, dt, ffn_ws_bytes(batch, hidden, inter, dt), bp) &&
+           !(stats && stats->n_union && bp->groups > 1);
+}
+
 ts_status check_moe_args(const float *x, const void *wr, const void *wg, const void *wu, const void *wd,
                          ts_dtype dt, int batch, int hidden, int inter, int E, int K, const float *out,
                          const int32_t *topk_idx, const float *topk_w, const ts_ffn_stats *stats, const void *ws,
@@ -2321,13 +2329,15 @@ ts_status moe_impl(const float *x, const void *wr, const void *wg, const void *w
     const size_t estride = (size_t)inter * (size_t)hidden;
     const bool batched = batch > 1 && tuned("batch_path") == 0 &&
                          (plan_batch(batch, hidden, inter, E, K, dt, &bp) ||
-                          plan_wide_moe(batch, hidden, inter, E, K, dt, &bp));
+                          plan_wide_moe(batch, hidden, inter, E, K, dt, &bp) ||
+                          (dt == TS_F32 && tuned("ffn_path") == 0 && exact_pays(batch, hidden, inter, E, K, dt) &&
+                           plan_exact(batch, hidden, inter, E, K, dt, moe_route_offset(batch, hidden, inter, E, K, dt), &bp)));
     // on the pipelined kernel each workgroup routes its own token (no router launch)
     const bool fold = !batched && slots_use_pipe(p, dense);
     // batched: the router also writes each token's x split for the matrix
     // cores, and the gate+up kernel gathers its group's tokens from it (no
     // dispatch kernel, one copy of x in L2 for all expert groups)
-    const bool xtok = batched && (bp.batch > kBxMaxTokens || tuned("bx_xtok") == 0);
+    const bool xtok = batched && (bp.wide || (bp.mode == kBxBf16x2 && tuned("bx_xtok") == 0));
     if (!fold) {
         if (dt == TS_F32) {
             launch_router<float>(p.nc, batch, st, x, wr, hidden, E, K, ridx, rw);
@@ -2449,6 +2459,8 @@ ts_status ts_ffn_sparse(const float *x, const void *w_gate, const void *w_up, co
         }
         return TS_OK;
     }
+    if (ts::plan_exact_ffn(batch, hidden, inter, wdtype, stats, &probe))
+        return ts::run_batch(x, w_gate, w_up, w_down_t, 0, nullptr, nullptr, probe, out, stats, 0, ws, st, false);
     return ts::run_slots(x, w_gate, w_up, w_down_t, nullptr, 0, wdtype, false, p, out, nullptr, stats, ws, st);
 }
 
@@ -2480,8 +2492,13 @@ ts_status ts_ffn_sparse_act(const float *x, const void *w_gate, const void *w_up
     ts_status s = ts::check_ffn_args(x, w_gate, w_up, w_down_t, wdtype, batch, hidden, inter, out, stats, ws,
                                      ws_bytes, &p);
     if (s != TS_OK) return s;
-    return ts::run_fused(x, w_gate, w_up, w_down_t, nullptr, 0, wdtype, false, p, out, nullptr, stats, ws,
-                         static_cast<hipStream_t>(stream), true, nullptr, 1, tau);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    ts::BatchPlan bp;
+    if (ts::plan_exact_ffn(batch, hidden, inter, wdtype, stats, &bp))
+        return ts::run_batch(x, w_gate, w_up, w_down_t, 0, nullptr, nullptr, bp, out, stats, 0, ws, st, false, false, 1,
+                             tau);
+    return ts::run_fused(x, w_gate, w_up, w_down_t, nullptr, 0, wdtype, false, p, out, nullptr, stats, ws, st, true,
+                         nullptr, 1, tau);
 }
 
 ts_status ts_ffn_dense(const float *x, const void *w_gate, const void *w_up, const void *w_down_t, ts_dtype wdtype,
@@ -2506,6 +2523,8 @@ ts_status ts_ffn_dense(const float *x, const void *w_gate, const void *w_up, con
         }
         return TS_OK;
     }
+    if (ts::plan_exact_ffn(batch, hidden, inter, wdtype, nullptr, &probe))
+        return ts::run_batch(x, w_gate, w_up, w_down_t, 0, nullptr, nullptr, probe, out, nullptr, 0, ws, st, true);
     return ts::run_slots(x, w_gate, w_up, w_down_t, nullptr, 0, wdtype, true, p, out, nullptr, nullptr, ws, st);
 }
 

@@ -205,8 +205,8 @@ void batch_layout(BatchPlan &q) {
     off = align256(off + G * sizeof(int32_t));
     q.off_tslot = off;   // (group, slot) of each (token, routed rank)
     off = align256(off + (size_t)q.batch * q.top_k * 2 * sizeof(int32_t));
-    q.off_xhl = off;     // x in bf16 parts: [G][parts][tok][hpad]
-    off = align256(off + G * P * q.tok * q.hpad * sizeof(uint16_t));
+    q.off_xhl = off;     // x in 16-bit parts: [G][xparts][tok][hpad]
+    off = align256(off + G * q.xparts * q.tok * q.hpad * sizeof(uint16_t));
     q.off_cnt = off;     // per tile: |union G|, |union A|
     off = align256(off + G * T * 2 * sizeof(int32_t));
     q.off_arow = off;    // per tile: row (within the tile) of each of its 32 active slots, bytes
@@ -273,7 +273,8 @@ bool plan_wide(int batch, int hidden, int inter, int experts, int top_k, int tok
     if ((unsigned long long)inter * (unsigned long long)hidden * 2ull >= (1ull << 32) - 16) return false;
     BatchPlan q;
     q.wide = true;
-    q.parts = parts;
+    q.parts = q.xparts = parts;
+    q.mode = parts == 3 ? kBxBf16x3 : kBxBf16x2;
     q.batch = batch;
     q.hidden = hidden;
     q.inter = inter;
@@ -317,6 +318,65 @@ bool plan_wide_moe(int batch, int hidden, int inter, int experts, int top_k, ts_
     if (check_moe_dims(batch, hidden, inter, experts, top_k, dt) != TS_OK || batch <= kBxMaxTokens) return false;
     return plan_wide(batch, hidden, inter, experts, top_k, 64, 3, dt,
                      moe_route_offset(batch, hidden, inter, experts, top_k, dt), p);
+}
+
+// The single-token kernels read a weight set once per token (or routed
+// pair), the batched ones once: about one matrix's bytes per saved reading,
+// against two more launches and a longer chain.  Measured per layer, batched
+// against single-token: fp32 41 MB matrices, 2 tokens 30.5 / 28.6 us, 6
+// tokens 39 / 65; 3.7 MB, 4 tokens 21.6 / 17.5; bf16 (gate-only ReLU) 117 MB,
+// 2 tokens 57 / 43, 4 tokens 61 / 80; 8 MB, 16 tokens 30 / 24.
+bool exact_pays(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt) {
+    const long long saved = (long long)batch * top_k - experts;
+    const long long line = (dt == TS_F32 ? 64LL : 240LL) << 20;
+    return saved > 0 && saved * inter * hidden * esize(dt) >= line;
+}
+
+bool plan_exact(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt, size_t limit, BatchPlan *p) {
+    if (check_moe_dims(batch, hidden, inter, experts, top_k, dt) != TS_OK || batch < 2) return false;
+    // row offsets are 32-bit byte offsets into one matrix
+    if ((unsigned long long)inter * (unsigned long long)hidden * esize(dt) >= (1ull << 32) - 16) return false;
+    if (dt == TS_BF16 && experts == 1 && batch > kWdMinTokens &&
+        plan_wide(batch, hidden, inter, 1, 1, 64, 3, dt, limit, p))
+        return true;
+    BatchPlan q;
+    q.batch = batch;
+    q.hidden = hidden;
+    q.inter = inter;
+    q.top_k = top_k;
+    q.experts = experts;
+    int slots = batch;
+    if (experts > 1) slots = std::min(batch, 2 * ((batch * top_k + experts - 1) / experts));
+    if (dt == TS_F32) {
+        q.mode = kBxF32;
+        q.tok = slots <= 16 ? 16 : 32;
+    } else {
+        q.mode = kBxBf16x3;
+        q.tok = slots <= 8 ? 8 : 16;
+        q.parts = 3;
+        q.xparts = q.tok == 8 ? 4 : 3;
+    }
+    q.rows = dt == TS_F32 && experts == 1 && top_k == 1 && batch <= kRowsMaxTokens;
+    q.vpe = (batch + q.tok - 1) / q.tok;
+    q.groups = experts * q.vpe;
+    q.bpad = q.tok;
+    const int quant = kBxKQuant * 2 / esize(dt);
+    q.hpad = (hidden + quant - 1) / quant * quant;
+    q.ntiles = (inter + kBxRows - 1) / kBxRows;
+    q.nslices = (hidden + kBxSliceCols - 1) / kBxSliceCols;
+    int want = g_down_chunks.load();
+    if (want <= 0) want = std::max(1, 256 / (q.nslices * experts));
+    for (; want >= 1; want /= 2) {
+        q.nchunks = std::min(want, q.ntiles);
+        q.tpc = std::min((q.ntiles + q.nchunks - 1) / q.nchunks, bx_down_tiles(q.tok));
+        q.nchunks = (q.ntiles + q.tpc - 1) / q.tpc;
+        batch_layout(q);
+        if (q.total <= limit) {
+            *p = q;
+            return true;
+        }
+    }
+    return false;
 }
 
 // Chunk of list entries per workgroup: enough workgroups for one per compute

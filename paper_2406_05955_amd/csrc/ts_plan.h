@@ -108,6 +108,11 @@ constexpr int bx_down_tiles(int tok) { return tok == 32 ? 224 : 64; }
 constexpr int bx_group_at(int gi, int G, int vpe) { return (gi % (G / vpe)) * vpe + gi / (G / vpe); }
 constexpr int kBxKQuant = 1024;   // the hidden dimension is padded to this (4 waves x 2 batches x 128)
 
+// Operand modes of the one-pass batched kernels.
+constexpr int kBxBf16x2 = 0;  // bf16 weights, x and Combined as two bf16 parts (16 significant bits)
+constexpr int kBxBf16x3 = 1;  // bf16 weights, three parts: all 24 bits of the fp32 values
+constexpr int kBxF32 = 2;     // fp32 weights and operands (v_mfma_f32_16x16x4_f32)
+
 // A "group" is one weight set with up to `tok` of its tokens.  The FFN has
 // one group holding the batch.  In the MoE layer each expert's token list
 // (known only on the device) is cut into `vpe` groups of `tok` consecutive
@@ -126,7 +131,10 @@ struct BatchPlan {
     int nchunks = 0;     // tile chunks per group in the down kernel
     int tpc = 0;         // tiles per chunk (<= bx_down_tiles(tok), wide: wd_down_tiles)
     bool wide = false;   // the workgroup-tiled kernels of ts_wide.hip
-    int parts = 2;       // bf16 parts of x and Combined (3: all 24 bits)
+    int mode = kBxBf16x2;
+    bool rows = false;   // gate + up by the row streams of ts_rows.hip
+    int parts = 2;       // 16-bit parts of Combined (mode kBxF32: the fp32 value takes the room of two)
+    int xparts = 2;      // and of x (packed fragments of three parts: 4)
     size_t off_gcount = 0, off_tslot = 0, off_xhl = 0, off_cnt = 0, off_arow = 0, off_hfrag = 0;
     size_t off_gmask = 0, off_amask = 0, off_partial = 0, off_union = 0;
     size_t total = 0;
@@ -140,6 +148,14 @@ struct BatchPlan {
 // workspace that the shape's other plans need, so workspace sizes do not
 // depend on it.
 constexpr int kWdMinTokens = 16;
+constexpr int kRowsMaxTokens = 8;  // fp32 row streams (ts_rows.hip): tokens whose x fits LDS
+
+// Batches through the fp32-exact modes: fp32 weights, and the activation
+// forms whose other route is the single-token kernels.  `limit`: workspace
+// bytes that the plan has to fit.
+bool exact_pays(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt);
+bool plan_exact(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt, size_t limit, BatchPlan *p);
+
 // 32-row tiles per down workgroup at most: its row list shares LDS with the
 // staging (the three-part MoE kernel: half a 14336-neuron expert, as bx_down).
 constexpr int wd_down_tiles(int tok, int parts) { return tok <= 64 && parts == 3 ? 224 : 64; }

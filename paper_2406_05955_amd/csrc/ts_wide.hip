@@ -523,33 +523,7 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_down(BxArgs a) {
     const int ntc = min(a.tpc, a.ntiles - t0);
     const size_t tbase = (size_t)g * a.ntiles + t0;
 
-    // ---- the chunk's row list (wave 0 scans the tiles' active counts)
-    if (wave == 0) {
-        int base = 0;
-        for (int t = 0; t < ntc; t += 64) {
-            const int v = t + lane < ntc ? a.cnt[(tbase + t + lane) * 2 + 1] : 0;
-            int inc = v;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int u = __shfl_up(inc, o, 64);
-                if (lane >= o) inc += u;
-            }
-            if (t + lane < ntc) s_pre[t + lane] = base + inc - v;
-            base += __shfl(inc, 63, 64);
-        }
-        if (lane == 0) s_pre[ntc] = base;
-    }
-    __syncthreads();
-    const int total = s_pre[ntc];
-    const int nblk = (total + KB - 1) / KB;
-    for (int e = tid; e < ntc * kBxRows; e += kWdThreads) {
-        const int t = e / kBxRows, s = e % kBxRows;
-        const int base = s_pre[t];
-        if (s < s_pre[t + 1] - base)
-            s_ent[base + s] = ((uint32_t)t << 10) | ((uint32_t)s << 5) | (uint32_t)(a.arow[tbase * kBxRows + e] & 31);
-    }
-    for (int e = total + tid; e < nblk * KB; e += kWdThreads) s_ent[e] = kPadRow;
-    __syncthreads();
+    const int nblk = bx_list_rows<kWdThreads, KB>(a, tbase, ntc, s_pre, s_ent);
 
     const uint16_t *wde = reinterpret_cast<const uint16_t *>(a.wd) + (size_t)(g / a.vpe) * a.expert_stride;
     const __amdgpu_buffer_rsrc_t rwd = make_rsrc(wde, (uint32_t)a.I * (uint32_t)H * 2u);
@@ -693,6 +667,10 @@ void launch_wide_down_cw(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
 
 void launch_wide_prep(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     const dim3 grid((unsigned)((p.groups * (p.hpad / 32) * (p.tok / 16) * 64 + 255) / 256));
+    if (p.parts == 3) {
+        launch("batch_prep", wd_prep<64, 3>, grid, dim3(256), st, a);
+        return;
+    }
     switch (p.tok) {
     case 32: launch("batch_prep", wd_prep<32, 2>, grid, dim3(256), st, a); break;
     case 64: launch("batch_prep", wd_prep<64, 2>, grid, dim3(256), st, a); break;
@@ -705,7 +683,8 @@ void launch_wide_prep(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
 // and bx_down 58.0 / 28.8), 64 tokens 55 / 34.6 (85.8 / 42.7), 256 tokens
 // 113 / 67 (four passes of 64: 327 / 168).
 void launch_wide_gate_up(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
-    if (p.parts == 3) launch_wide_gate_moe<64, 3, 128, 1>(p, a, st);
+    if (p.parts == 3 && a.topk) launch_wide_gate_moe<64, 3, 128, 1>(p, a, st);
+    else if (p.parts == 3) launch_wide_gate<64, 3, 64, 1>(p, a, st);
     else if (p.tok == 128) launch_wide_gate<128, 2, 128, 2>(p, a, st);
     else if (p.tok == 64) launch_wide_gate<64, 2, 64, 2>(p, a, st);
     else launch_wide_gate<32, 2, 64, 4>(p, a, st);

@@ -1,0 +1,88 @@
+"""Parity of the fp32-exact batched kernels (fp32 weights; the gate-only ReLU
+over bf16 weights) against the fp64 oracle at the single-token kernels'
+tolerances, at shapes just past the size rule that selects them: the row
+streams (up to 8 fp32 tokens, 4 / 6 / 8 token variants, one and two segments
+per row), the fp32 matrix-core kernels (16 and 32 slots, several groups),
+the three-part kernels (8 and 16 slots; 64 slots, several groups), hidden
+and inter ragged, the dense comparator, the report and a reused workspace
+full of NaN."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import check_ffn_output, ffn_inputs_to_dev, rel_l2, to_dev
+from paper_2406_05955_amd import synth
+from test_gpu_act import check as check_act
+from test_gpu_ffn import check_ffn
+from test_gpu_moe import check_moe
+
+pytestmark = pytest.mark.gpu
+
+ts = pytest.importorskip("paper_2406_05955_amd.binding") if torch.cuda.is_available() else None
+
+
+def launches(fn, kernel):
+    ts.prof_reset()
+    ts.prof_enable(True)
+    try:
+        fn()
+        torch.cuda.synchronize()
+        return ts.prof_read(kernel)[0]
+    finally:
+        ts.prof_enable(False)
+        ts.prof_reset()
+
+
+@pytest.mark.parametrize("B,H,I,bias", [(2, 4096, 4101, -0.84), (4, 1500, 3757, -0.84), (5, 2052, 2085, 8.0),
+                                        (6, 516, 6600, -0.84), (8, 4096, 600, 0.0), (9, 1032, 2105, -0.84),
+                                        (16, 260, 4400, -1.5), (17, 516, 2047, -0.84), (33, 260, 2050, -0.84)])
+def test_exact_f32(B, H, I, bias):
+    inp = synth.make_ffn(B, H, I, gate_bias=bias, dtype=synth.F32, seed=[81, B, H, I])
+    out, st, ref = check_ffn(inp)
+    x, wg, wu, wd = ffn_inputs_to_dev(inp)
+    ws = torch.empty(ts.ffn_workspace_bytes(B, H, I, ts.TS_F32), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xFF)  # NaN in every type: nothing stale may be read
+    again = ts.ffn_sparse(x, wg, wu, wd, ws=ws)
+    ws.fill_(0xFF)
+    dense = ts.ffn_dense(x, wg, wu, wd, ws=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int32), again.view(torch.int32))
+    check_ffn_output(dense.cpu().numpy(), ref.y, inp.x, inp.w_gate, inp.w_up, inp.w_down_t, ref.g, ref.u,
+                     what=f"dense B={B} H={H} I={I}")
+    assert launches(lambda: ts.ffn_sparse(x, wg, wu, wd), "batch_down") == 1  # (the rule took this route)
+
+
+@pytest.mark.parametrize("B,H,I,dtype,tau", [(8, 4096, 4485, synth.BF16, 0.2), (9, 2056, 7700, synth.BF16, 0.0),
+                                             (16, 2056, 4085, synth.BF16, 0.44), (17, 2056, 3830, synth.BF16, 0.1),
+                                             (65, 1032, 1910, synth.BF16, -0.3), (130, 520, 1877, synth.BF16, 0.1),
+                                             (6, 2052, 2000, synth.F32, 0.25), (12, 1032, 1800, synth.F32, -0.2)])
+def test_exact_act(B, H, I, dtype, tau):
+    """tau < 0 as well: a token slot past the batch must not open a gate."""
+    inp = synth.make_ffn(B, H, I, gate_bias=-0.84, dtype=dtype, seed=[82, B, H, I])
+    out, ref = check_act(inp, tau)
+    assert rel_l2(out.cpu().numpy(), ref.y) <= 1e-5
+    x, wg, wu, wd = ffn_inputs_to_dev(inp)
+    assert launches(lambda: ts.ffn_sparse_act(x, wg, wu, wd, ts.TS_ACT_RELU_GATE, tau), "batch_down") == 1
+
+
+@pytest.mark.parametrize("B,H,I,E,K", [(16, 516, 1205, 4, 2), (40, 260, 905, 8, 2), (40, 128, 3300, 2, 2)])
+def test_exact_moe_f32(B, H, I, E, K):
+    m = synth.make_moe(B, H, I, E, K, gate_bias=-0.84, dtype=synth.F32, seed=[83, B, H, I, E, K])
+    check_moe(m)
+    check_moe(m, dense=True)
+    args = [to_dev(m.x), to_dev(m.w_router), to_dev(m.w_gate), to_dev(m.w_up), to_dev(m.w_down_t)]
+    assert launches(lambda: ts.moe_sparse(*args, K), "batch_down") == 1
+
+
+def test_exact_union_counts():
+    """The union report of a single-group batch on this route."""
+    inp = synth.make_ffn(6, 1032, 3400, gate_bias=-0.84, dtype=synth.F32, seed=84)
+    ref = oracle.ffn(inp.x, inp.w_gate, inp.w_up, inp.w_down_t, inp.dtype)
+    x, wg, wu, wd = ffn_inputs_to_dev(inp)
+    _, st = ts.ffn_sparse(x, wg, wu, wd, union=True)
+    torch.cuda.synchronize()
+    near = ((np.abs(ref.g) < 1e-6) | (np.abs(ref.u) < 1e-6)).any(axis=0).sum()
+    got = st["n_union"].cpu().tolist()
+    assert abs(got[0] - int((ref.g > 0).any(axis=0).sum())) <= near
+    assert abs(got[1] - int(((ref.g > 0) & (ref.u > 0)).any(axis=0).sum())) <= near

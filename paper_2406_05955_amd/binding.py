@@ -100,14 +100,26 @@ def _check(code: int, where: str):
         raise TSError(code, where, detail)
 
 
+# A small call's time is the host's: per call at the 512 x 1792 layer, tensor
+# checks 2.2 us, the stream object 2.9, pointer objects 1.0, a workspace size
+# that the caller's own workspace makes needless 0.5, of 15.1 (the library's
+# two launches 8.2).  So pointers are passed as plain integers (the argument
+# types convert them), the current stream is asked for as a handle where this
+# torch offers it, and well-formed tensors pass one combined test.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_cur_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _cur_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_cur_device())
 
 
 def wdtype_of(t: torch.Tensor) -> int:
@@ -131,7 +143,27 @@ def _need_cuda(*ts):
             raise ValueError(f"tensors on different devices ({dev}, {t.device})")
 
 
+def _on(t, d):
+    return t.is_cuda and t.get_device() == d and t.is_contiguous()
+
+
+_f32, _bf16 = torch.float32, torch.bfloat16
+
+
 def _check_tensors(x, w_gate, w_up, w_down_t, out, w_router=None):
+    """Raises unless the tensors are what _explain_tensors describes."""
+    xs, ws, dt, d = x.shape, w_gate.shape, w_gate.dtype, x.get_device()
+    if (x.dtype is _f32 and len(xs) == 2 and (dt is _bf16 or dt is _f32)
+            and len(ws) == (2 if w_router is None else 3) and ws[-1] == xs[1]
+            and w_up.dtype is dt and w_up.shape == ws and w_down_t.dtype is dt and w_down_t.shape == ws
+            and (out is None or (out.dtype is _f32 and out.shape == xs and _on(out, d)))
+            and _on(x, d) and _on(w_gate, d) and _on(w_up, d) and _on(w_down_t, d)
+            and (w_router is None or (w_router.dtype is dt and w_router.shape == (ws[0], xs[1]) and _on(w_router, d)))):
+        return
+    _explain_tensors(x, w_gate, w_up, w_down_t, out, w_router)
+
+
+def _explain_tensors(x, w_gate, w_up, w_down_t, out, w_router=None):
     """What the C ABI cannot check (it sees only pointers and the sizes passed
     with them): x float32 [B][H]; W_gate, W_up, W_down_t one dtype and one
     shape, [I][H] or, for the MoE layer, [E][I][H] with the router [E][H] of
@@ -168,15 +200,15 @@ def moe_workspace_bytes(batch: int, hidden: int, inter: int, n_experts: int, top
     return int(lib.ts_moe_workspace_bytes(batch, hidden, inter, n_experts, top_k, wdtype))
 
 
-def _workspace(nbytes: int, device, ws):
+def _workspace(sizer, device, ws, *sizes):
     """The caller's workspace (any dtype; its size in bytes is passed on), or
-    a new one of the size the library asks for."""
+    a new one of the size the library asks for, sizer(*sizes)."""
     if ws is not None:
         _need_cuda(ws)
         if ws.device != device:
             raise ValueError(f"workspace on {ws.device}, tensors on {device}")
         return ws
-    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+    return torch.empty(max(sizer(*sizes), 256), dtype=torch.uint8, device=device)
 
 
 def _nbytes(t):
@@ -206,14 +238,15 @@ def ffn_sparse(x, w_gate, w_up, w_down_t, out=None, stats: bool = False, union: 
     dt = wdtype_of(w_gate)
     if out is None:
         out = torch.empty(B, H, dtype=torch.float32, device=x.device)
-    ws = _workspace(ffn_workspace_bytes(B, H, I, dt), x.device, ws)
+    ws = _workspace(ffn_workspace_bytes, x.device, ws, B, H, I, dt)
     st, d = _stats_struct(B, I, x.device, stats or union)
     if union:
         d["n_union"] = torch.empty(2, dtype=torch.int32, device=x.device)
         st.n_union = _ptr(d["n_union"])
     code = lib.ts_ffn_sparse(_ptr(x), _ptr(w_gate), _ptr(w_up), _ptr(w_down_t), dt, B, H, I, _ptr(out),
                              ctypes.byref(st) if st is not None else None, _ptr(ws), _nbytes(ws), _stream(stream))
-    _check(code, "ts_ffn_sparse")
+    if code:
+        _check(code, "ts_ffn_sparse")
     return (out, d) if d is not None else out
 
 
@@ -238,7 +271,8 @@ def ffn_sparse_noalloc(x, w_gate, w_up, w_down_t, out=None, stats: bool = False,
         st.n_union = _ptr(d["n_union"])
     code = lib.ts_ffn_sparse_noalloc(_ptr(x), _ptr(w_gate), _ptr(w_up), _ptr(w_down_t), dt, B, H, I, _ptr(out),
                                      ctypes.byref(st) if st is not None else None, _stream(stream))
-    _check(code, "ts_ffn_sparse_noalloc")
+    if code:
+        _check(code, "ts_ffn_sparse_noalloc")
     return (out, d) if d is not None else out
 
 
@@ -256,7 +290,7 @@ def ffn_sparse_act(x, w_gate, w_up, w_down_t, act: int, tau: float = 0.0, out=No
     dt = wdtype_of(w_gate)
     if out is None:
         out = torch.empty(B, H, dtype=torch.float32, device=x.device)
-    ws = _workspace(ffn_workspace_bytes(B, H, I, dt), x.device, ws)
+    ws = _workspace(ffn_workspace_bytes, x.device, ws, B, H, I, dt)
     st, d = _stats_struct(B, I, x.device, stats or union)
     if union:
         d["n_union"] = torch.empty(2, dtype=torch.int32, device=x.device)
@@ -264,7 +298,8 @@ def ffn_sparse_act(x, w_gate, w_up, w_down_t, act: int, tau: float = 0.0, out=No
     code = lib.ts_ffn_sparse_act(_ptr(x), _ptr(w_gate), _ptr(w_up), _ptr(w_down_t), dt, B, H, I, int(act),
                                  float(tau), _ptr(out), ctypes.byref(st) if st is not None else None, _ptr(ws),
                                  _nbytes(ws), _stream(stream))
-    _check(code, "ts_ffn_sparse_act")
+    if code:
+        _check(code, "ts_ffn_sparse_act")
     return (out, d) if d is not None else out
 
 
@@ -277,12 +312,13 @@ def ffn_sparse_topk(x, w_gate, w_up, w_down_t, keep: int, out=None, stats: bool 
     dt = wdtype_of(w_gate)
     if out is None:
         out = torch.empty(B, H, dtype=torch.float32, device=x.device)
-    ws = _workspace(ffn_workspace_bytes(B, H, I, dt), x.device, ws)
+    ws = _workspace(ffn_workspace_bytes, x.device, ws, B, H, I, dt)
     st, d = _stats_struct(B, I, x.device, stats)
     code = lib.ts_ffn_sparse_topk(_ptr(x), _ptr(w_gate), _ptr(w_up), _ptr(w_down_t), dt, B, H, I, int(keep),
                                   _ptr(out), ctypes.byref(st) if st is not None else None, _ptr(ws), _nbytes(ws),
                                   _stream(stream))
-    _check(code, "ts_ffn_sparse_topk")
+    if code:
+        _check(code, "ts_ffn_sparse_topk")
     return (out, d) if d is not None else out
 
 
@@ -294,10 +330,11 @@ def ffn_dense(x, w_gate, w_up, w_down_t, out=None, ws=None, stream=None):
     dt = wdtype_of(w_gate)
     if out is None:
         out = torch.empty(B, H, dtype=torch.float32, device=x.device)
-    ws = _workspace(ffn_workspace_bytes(B, H, I, dt), x.device, ws)
+    ws = _workspace(ffn_workspace_bytes, x.device, ws, B, H, I, dt)
     code = lib.ts_ffn_dense(_ptr(x), _ptr(w_gate), _ptr(w_up), _ptr(w_down_t), dt, B, H, I, _ptr(out), _ptr(ws),
                             _nbytes(ws), _stream(stream))
-    _check(code, "ts_ffn_dense")
+    if code:
+        _check(code, "ts_ffn_dense")
     return out
 
 
@@ -317,7 +354,7 @@ def ffn_sparse_given(x, w_gate, w_up, w_down_t, idx, count, out=None, stats: boo
     maxc = idx.shape[1]
     if out is None:
         out = torch.empty(B, H, dtype=torch.float32, device=x.device)
-    ws = _workspace(ffn_given_workspace_bytes(B, H, I, maxc, dt), x.device, ws)
+    ws = _workspace(ffn_given_workspace_bytes, x.device, ws, B, H, I, maxc, dt)
     d = st = None
     if stats:
         d = {"n_gate": torch.empty(B, dtype=torch.int32, device=x.device),
@@ -326,7 +363,8 @@ def ffn_sparse_given(x, w_gate, w_up, w_down_t, idx, count, out=None, stats: boo
     code = lib.ts_ffn_sparse_given(_ptr(x), _ptr(w_gate), _ptr(w_up), _ptr(w_down_t), dt, B, H, I, _ptr(idx),
                                    _ptr(count), maxc, _ptr(out), ctypes.byref(st) if st is not None else None,
                                    _ptr(ws), _nbytes(ws), _stream(stream))
-    _check(code, "ts_ffn_sparse_given")
+    if code:
+        _check(code, "ts_ffn_sparse_given")
     return (out, d) if d is not None else out
 
 
@@ -342,17 +380,19 @@ def moe_sparse(x, w_router, w_gate, w_up, w_down_t, top_k: int, out=None, stats:
         out = torch.empty(B, H, dtype=torch.float32, device=x.device)
     idx = torch.empty(B, top_k, dtype=torch.int32, device=x.device)
     wts = torch.empty(B, top_k, dtype=torch.float32, device=x.device)
-    ws = _workspace(moe_workspace_bytes(B, H, I, E, top_k, dt), x.device, ws)
+    ws = _workspace(moe_workspace_bytes, x.device, ws, B, H, I, E, top_k, dt)
     if dense:
         code = lib.ts_moe_dense(_ptr(x), _ptr(w_router), _ptr(w_gate), _ptr(w_up), _ptr(w_down_t), dt, B, H, I, E,
                                 top_k, _ptr(out), _ptr(idx), _ptr(wts), _ptr(ws), _nbytes(ws), _stream(stream))
-        _check(code, "ts_moe_dense")
+        if code:
+            _check(code, "ts_moe_dense")
         return out, idx, wts
     st, d = _stats_struct(B * top_k, I, x.device, stats)
     code = lib.ts_moe_sparse(_ptr(x), _ptr(w_router), _ptr(w_gate), _ptr(w_up), _ptr(w_down_t), dt, B, H, I, E,
                              top_k, _ptr(out), _ptr(idx), _ptr(wts), ctypes.byref(st) if st is not None else None,
                              _ptr(ws), _nbytes(ws), _stream(stream))
-    _check(code, "ts_moe_sparse")
+    if code:
+        _check(code, "ts_moe_sparse")
     return (out, idx, wts, d) if d is not None else (out, idx, wts)
 
 

@@ -523,9 +523,10 @@ __global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up(BxArgs a) {
                         if constexpr (S::F32) {
                             reinterpret_cast<float *>(s_h[slot])[t] = hv[mt][nt][i];
                         } else {
+                            float v = hv[mt][nt][i];
 #pragma unroll
                             for (int p = 0; p < S::P; ++p)
-                                reinterpret_cast<uint16_t *>(s_h[slot])[p * TOK + t] = (uint16_t)bf16_part(hv[mt][nt][i], p);
+                                reinterpret_cast<uint16_t *>(s_h[slot])[p * TOK + t] = (uint16_t)bf16_take<S::P>(v);
                         }
                     }
                 }

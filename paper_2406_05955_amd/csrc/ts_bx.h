@@ -60,17 +60,10 @@ __device__ __forceinline__ uint32_t bf16_sel(float v, int p) {
     uint32_t out = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-        const uint32_t b = bf16_bits(v);
+        const uint32_t b = bf16_take<P>(v);
         out = q == p ? b : out;
-        v -= __uint_as_float(b << 16);  // exact
     }
     return out;
-}
-
-// Part p of v: the bf16 rounding of what the earlier parts leave.
-__device__ __forceinline__ uint32_t bf16_part(float v, int p) {
-    for (int q = 0; q < p; ++q) v -= __uint_as_float(bf16_bits(v) << 16);  // exact
-    return bf16_bits(v);
 }
 
 struct BxArgs {

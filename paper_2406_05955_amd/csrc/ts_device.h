@@ -137,6 +137,27 @@ __device__ __forceinline__ uint32_t bf16_bits(float f) {
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
+// Takes the next of P bf16 parts of v (returned) and leaves the rest in v.
+// Three parts stand in for products of the fp32 value itself, so they keep
+// its whole range: an infinity or a NaN is its first part alone (its rest
+// would be NaN), and a value above the largest bf16 takes that one instead of
+// rounding to infinity.  (Both are selects beside the rounding: they measure
+// nothing in the kernels that split.)
+template <int P>
+__device__ __forceinline__ uint32_t bf16_take(float &v) {
+    uint32_t b = bf16_bits(v);
+    if constexpr (P == 3) {
+        const uint32_t u = __float_as_uint(v), mag = u & 0x7FFFFFFFu;
+        const bool fin = mag < 0x7F800000u;
+        if (fin && (b & 0x7FFFu) == 0x7F80u) b -= 1u;
+        if (!fin) b = (u >> 16) | (mag > 0x7F800000u ? 0x40u : 0u);
+        v = fin ? v - __uint_as_float(b << 16) : 0.f;  // exact
+    } else {
+        v -= __uint_as_float(b << 16);  // exact
+    }
+    return b;
+}
+
 // x = hi + lo as two bf16 parts (16 significant bits together), the matrix
 // cores' operands for fp32-level products with bf16 weights.
 __device__ __forceinline__ void split_hi_lo(float x, uint32_t &hi, uint32_t &lo) {

@@ -1828,10 +1828,9 @@ __global__ __launch_bounds__(256) void moe_router(const float *__restrict__ x, c
                         uint32_t o[4];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const uint32_t b0 = bf16_bits(r[2 * e]), b1 = bf16_bits(r[2 * e + 1]);
+                            const uint32_t b0 = xs_parts == 3 ? bf16_take<3>(r[2 * e]) : bf16_take<2>(r[2 * e]);
+                            const uint32_t b1 = xs_parts == 3 ? bf16_take<3>(r[2 * e + 1]) : bf16_take<2>(r[2 * e + 1]);
                             o[e] = b0 | (b1 << 16);
-                            r[2 * e] -= __uint_as_float(b0 << 16);  // exact
-                            r[2 * e + 1] -= __uint_as_float(b1 << 16);
                         }
                         row[xs_parts * c + p] = u32x4{o[0], o[1], o[2], o[3]};
                     }

@@ -119,10 +119,8 @@ __global__ __launch_bounds__(256) void wd_prep(BxArgs a) {
         uint32_t o[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const uint32_t b0 = bf16_bits(v[2 * e]), b1 = bf16_bits(v[2 * e + 1]);
+            const uint32_t b0 = bf16_take<P>(v[2 * e]), b1 = bf16_take<P>(v[2 * e + 1]);
             o[e] = b0 | (b1 << 16);
-            v[2 * e] -= __uint_as_float(b0 << 16);      // exact
-            v[2 * e + 1] -= __uint_as_float(b1 << 16);
         }
         dst[p * 64] = u32x4{o[0], o[1], o[2], o[3]};
     }
@@ -451,9 +449,7 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
                     float v = cg[m][n][i];
 #pragma unroll
                     for (int p = 0; p < P; ++p) {
-                        const uint32_t h = bf16_bits(v);
-                        dst[p * TOK + t] = (uint16_t)h;
-                        v -= __uint_as_float(h << 16);
+                        dst[p * TOK + t] = (uint16_t)bf16_take<P>(v);
                     }
                 }
             }

@@ -86,3 +86,40 @@ def test_exact_union_counts():
     got = st["n_union"].cpu().tolist()
     assert abs(got[0] - int((ref.g > 0).any(axis=0).sum())) <= near
     assert abs(got[1] - int(((ref.g > 0) & (ref.u > 0)).any(axis=0).sum())) <= near
+
+
+@pytest.mark.parametrize("entry,B", [("act", 8), ("act", 12), ("act", 40), ("moe", 130)])
+def test_exact_whole_fp32_range(entry, B):
+    """Values that three bf16 parts could lose: an infinity, a NaN whose
+    payload is all ones, and one above the largest bf16 (whose first part must
+    not round to infinity).  Every token of the batch gives what it gives
+    alone (the single-token kernels' fp32 products)."""
+    H, I, E = (4096, 4485, 1) if entry == "act" else (256, 520, 2)
+    m = synth.make_moe(B, H, I, E, 1, gate_bias=-0.84, dtype=synth.BF16, seed=[85, B])
+    x, wr, wg, wu, wd = (to_dev(a) for a in (m.x, m.w_router, m.w_gate, m.w_up, m.w_down_t))
+    big = 3.4e38  # rounds to infinity in bf16
+    x[2, 9], x[3, 7] = big, -big
+    if entry == "act":  # (either would make the router's logits NaN)
+        x[1, 5] = float("inf")
+        x[4, 3] = torch.full((1,), -1, dtype=torch.int32, device="cuda").view(torch.float32)[0]
+    # columns 5: inf times positive weights, a sum of infinities of one sign;
+    # 7 and 9: gates near 1e37, the up projections as without them
+    wg[:, :, 5], wu[:, :, 5], wd[:, :, :] = wg[:, :, 5].abs() + 0.01, wu[:, :, 5].abs() + 0.01, wd.abs() + 0.001
+    wu[:, :, 7], wu[:, :, 9] = 0.0, 0.0
+    wr[:, 7], wr[:, 9] = 0.0, 0.0
+
+    def call(v):
+        if entry == "act":
+            return ts.ffn_sparse_act(v, wg[0], wu[0], wd[0], ts.TS_ACT_RELU_GATE, 0.1)
+        return ts.moe_sparse(v, wr, wg, wu, wd, 1)[0]
+
+    got = call(x).cpu().numpy()
+    want = np.concatenate([call(x[t:t + 1].contiguous()).cpu().numpy() for t in range(B)])
+    assert np.isposinf(want[1]).all() or entry == "moe"
+    assert np.isfinite(want[2:4]).all() and np.abs(want[2:4]).max() > 1e30
+    assert np.array_equal(np.isfinite(got), np.isfinite(want))
+    for t in range(B):
+        f = np.isfinite(want[t])
+        assert np.array_equal(got[t][~f], want[t][~f], equal_nan=True), t
+        scale = np.abs(want[t][f]).max(initial=0.0)
+        assert np.abs(got[t][f] / max(scale, 1e-30) - want[t][f] / max(scale, 1e-30)).max(initial=0.0) <= 1e-5, t

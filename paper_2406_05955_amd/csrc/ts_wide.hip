@@ -80,6 +80,27 @@ __device__ __forceinline__ void wd_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Instruction order of a half stage that reads the next k-step's operands
+// (R LDS reads) while M matrix instructions contract the present one, and
+// writes W chunks of the next stage: spread over each other.  Left alone the
+// compiler moves every read next to its use, and the reads' time adds to the
+// matrix instructions' instead of hiding behind them.
+template <int R, int W, int M>
+__device__ __forceinline__ void wd_spread() {
+    constexpr int PER = R > 0 && (M - W) / R > 0 ? (M - W) / R : 1;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
+        __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);  // matrix
+    }
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 }  // namespace
 
 // x of every group's token slots as MFMA operand fragments in P parts (the
@@ -136,7 +157,7 @@ __global__ __launch_bounds__(256) void wd_prep(BxArgs a) {
 // tile then hits in L2, since both run on one XCD).
 // QSPLIT: the sums of the hidden dimension's quarters are added in
 // bx_gate_up's order, (q0 + q1) + (q2 + q3): the same bits.
-template <int TOK, int P, int NB, int D, bool GATHER, bool STREAM>
+template <int TOK, int P, int NB, int D, bool GATHER, bool STREAM, bool AHEAD>
 __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
     constexpr int KS = 2;                       // 32-wide k-steps per stage
     constexpr int NX = P * TOK / 16;            // x fragments per k-step
@@ -274,36 +295,41 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
 #pragma unroll
             for (int n = 0; n < NT; ++n) cg[m][n] = cu[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
+    // operand fragments of k-step s in register slot s: the reads of the next
+    // k-step are in flight while one is contracted
+    u32x4 fa[2][2 * MN], fb[2][NT * P];
     // the wave's n-tiles are wn, wn + 2, ...; the first NACT hold tokens
-    auto compute = [&](int buf, auto nac) {
+    auto load = [&](int buf, int s, auto nac) {
         constexpr int NACT = decltype(nac)::value;
         const u32x4 *sa = s_lds + buf * ABUF, *sb = s_lds + 2 * ABUF + buf * BBUF;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            u32x4 ag[MN], au[MN];
+        if constexpr (NACT > 0) {
 #pragma unroll
             for (int m = 0; m < MN; ++m) {
                 const int row = (wm * MN + m) * 16 + lm;
-                ag[m] = sa[wd_swz(row, 4 * s + lq)];
-                au[m] = sa[wd_swz(NB + row, 4 * s + lq)];
-            }
-#pragma unroll
-            for (int n = 0; n < NACT; ++n) {
-                u32x4 b[P];
-#pragma unroll
-                for (int p = 0; p < P; ++p) b[p] = sb[(s * NX + P * (2 * n + wn) + p) * 64 + lane];
-#pragma unroll
-                for (int p = 0; p < P; ++p)
-#pragma unroll
-                    for (int m = 0; m < MN; ++m) {
-                        f32x4 &g = LO && p ? cgl[LO ? m : 0][LO ? n : 0] : cg[m][n];
-                        f32x4 &v = LO && p ? cul[LO ? m : 0][LO ? n : 0] : cu[m][n];
-                        g = mfma_bf16(ag[m], b[p], g);
-                        v = mfma_bf16(au[m], b[p], v);
-                    }
+                fa[s][2 * m] = sa[wd_swz(row, 4 * s + lq)];
+                fa[s][2 * m + 1] = sa[wd_swz(NB + row, 4 * s + lq)];
             }
         }
+#pragma unroll
+        for (int n = 0; n < NACT; ++n)
+#pragma unroll
+            for (int p = 0; p < P; ++p) fb[s][P * n + p] = sb[(s * NX + P * (2 * n + wn) + p) * 64 + lane];
     };
+    auto contract = [&](int s, auto nac) {
+        constexpr int NACT = decltype(nac)::value;
+#pragma unroll
+        for (int n = 0; n < NACT; ++n)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int m = 0; m < MN; ++m) {
+                    f32x4 &g = LO && p ? cgl[LO ? m : 0][LO ? n : 0] : cg[m][n];
+                    f32x4 &v = LO && p ? cul[LO ? m : 0][LO ? n : 0] : cu[m][n];
+                    g = mfma_bf16(fa[s][2 * m], fb[s][P * n + p], g);
+                    v = mfma_bf16(fa[s][2 * m + 1], fb[s][P * n + p], v);
+                }
+    };
+    static_assert(KS == 2, "a register slot per k-step of a stage");
 
     constexpr int U = D > 2 ? D : 2;
     static_assert(4 % U == 0, "a quarter's stages (a multiple of 4) in whole rounds");
@@ -317,13 +343,26 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
     // the next stage goes from registers to the other buffer and its slot
     // takes a later stage (loads past the last stage are out of range: zeros)
     auto steps_n = [&](int s0, int s1, auto nac) {
+        constexpr int NACT = decltype(nac)::value;
+        constexpr int R = NACT ? 2 * MN + NACT * P : 0, M = 2 * MN * NACT * P;  // (of a k-step)
+        if (AHEAD && s0 == 0) load(0, 0, nac);
         for (int st = s0; st < s1; st += U) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                compute(u & 1, nac);
+                if constexpr (!AHEAD) load(u & 1, 0, nac);
+                load(u & 1, 1, nac);
+                contract(0, nac);
+                if constexpr (!AHEAD) contract(1, nac);
                 stash((u + 1) % D, (u + 1) & 1);
                 issue((u + 1) % D, st + u + 1 + D);
+                if constexpr (AHEAD) wd_spread<R, NA + NXL, M>();
                 wd_barrier();
+                if constexpr (AHEAD) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    load((u + 1) & 1, 0, nac);
+                    contract(1, nac);
+                    wd_spread<R, 0, M>();
+                }
             }
         }
     };
@@ -482,7 +521,7 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
 // blocks of 32; a block's W_down_t rows and Combined records go through LDS
 // (rows padded by 32 bytes, so a transposing read's four rows start on
 // different banks).  Waves: WC along the columns x 8 / WC along the tokens.
-template <int TOK, int P, int CW, int WC, int KS, int D, int MAXT, bool STREAM>
+template <int TOK, int P, int CW, int WC, int KS, int D, int MAXT, bool STREAM, bool AHEAD>
 __global__ __launch_bounds__(kWdThreads, 2) void wd_down(BxArgs a) {
     constexpr int WT = 8 / WC;
     constexpr int NC = CW / 16 / WC, NT = TOK / 16 / WT;  // tiles per wave
@@ -490,7 +529,7 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_down(BxArgs a) {
     constexpr int WCH = KB * CW / 8, HCH = KB * P * TOK / 8;  // 16-byte chunks per block
     constexpr int NW = WCH / kWdThreads, NH = (HCH + kWdThreads - 1) / kWdThreads;
     constexpr int WP = CW + 16, HP = P * TOK + 16;  // LDS row pitches (elements)
-    static_assert(WCH % kWdThreads == 0 && NC >= 1 && NT >= 1, "whole chunks per thread");
+    static_assert(KS <= 2 && WCH % kWdThreads == 0 && NC >= 1 && NT >= 1, "whole chunks per thread");
     __shared__ __attribute__((aligned(16))) uint16_t s_w[2][KB * WP], s_h[2][KB * HP];
     __shared__ uint32_t s_ent[(MAXT + KS - 1) * kBxRows];  // (tile within the chunk) << 10 | slot << 5 | row, or kPadRow
     __shared__ int s_pre[MAXT + 1];
@@ -564,41 +603,64 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_down(BxArgs a) {
     for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int n = 0; n < NT; ++n) acc[c][n] = accl[LO ? c : 0][LO ? n : 0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // fragments of k-step s of a stage in register slot `slot`
+    u32x4 wf[2][NC], hf[2][NT * P];
     // the wave's n-tiles are wtk, wtk + WT, ...
-    auto compute = [&](int buf, auto nac) {
+    auto load = [&](int buf, int s, int slot, auto nac) {
         constexpr int NACT = decltype(nac)::value;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            u32x4 wf[NC];
+        if constexpr (NACT > 0) {
 #pragma unroll
             for (int c = 0; c < NC; ++c)
-                wf[c] = wd_tr_frag(&s_w[buf][s * kBxRows * WP + 16 * (wc * NC + c)], WP, lane);
-#pragma unroll
-            for (int n = 0; n < NACT; ++n) {
-                u32x4 hf[P];
-#pragma unroll
-                for (int p = 0; p < P; ++p)
-                    hf[p] = wd_tr_frag(&s_h[buf][s * kBxRows * HP + p * TOK + 16 * (n * WT + wtk)], HP, lane);
-#pragma unroll
-                for (int p = 0; p < P; ++p)
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        f32x4 &v = LO && p ? accl[LO ? c : 0][LO ? n : 0] : acc[c][n];
-                        v = mfma_bf16(wf[c], hf[p], v);
-                    }
-            }
+                wf[slot][c] = wd_tr_frag(&s_w[buf][s * kBxRows * WP + 16 * (wc * NC + c)], WP, lane);
         }
+#pragma unroll
+        for (int n = 0; n < NACT; ++n)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                hf[slot][P * n + p] =
+                    wd_tr_frag(&s_h[buf][s * kBxRows * HP + p * TOK + 16 * (n * WT + wtk)], HP, lane);
+    };
+    auto contract = [&](int slot, auto nac) {
+        constexpr int NACT = decltype(nac)::value;
+#pragma unroll
+        for (int n = 0; n < NACT; ++n)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    f32x4 &v = LO && p ? accl[LO ? c : 0][LO ? n : 0] : acc[c][n];
+                    v = mfma_bf16(wf[slot][c], hf[slot][P * n + p], v);
+                }
     };
     constexpr int U = D > 2 ? D : 2;
     auto blocks = [&](auto nac) {
+        constexpr int NACT = decltype(nac)::value;
+        constexpr int R = NACT ? 2 * (NC + NACT * P) : 0, M = NC * NACT * P;  // (of a k-step)
+        if constexpr (AHEAD) load(0, 0, 0, nac);
         for (int b = 0; b < nblk; b += U) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (b + u < nblk) {  // uniform over the workgroup
-                    compute(u & 1, nac);
+                    if constexpr (AHEAD && KS == 2) {
+                        load(u & 1, 1, 1, nac);
+                        contract(0, nac);
+                        wd_spread<R, 0, M>();
+                    } else if constexpr (!AHEAD) {
+#pragma unroll
+                        for (int s = 0; s < KS; ++s) {
+                            load(u & 1, s, s, nac);
+                            contract(s, nac);
+                        }
+                    }
                     stash((u + 1) % D, (u + 1) & 1);
                     issue((u + 1) % D, b + u + 1 + D);
                     wd_barrier();
+                    if constexpr (AHEAD) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        load((u + 1) & 1, 0, KS == 2 ? 0 : (u + 1) & 1, nac);
+                        contract(KS == 2 ? 1 : u & 1, nac);
+                        wd_spread<R, 0, M>();
+                    }
                 }
             }
         }
@@ -636,27 +698,27 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_down(BxArgs a) {
 
 namespace {
 
-template <int TOK, int P, int NB, int D>
+template <int TOK, int P, int NB, int D, bool AHEAD>
 void launch_wide_gate(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     const int nwt = (p.ntiles + NB / kBxRows - 1) / (NB / kBxRows);
     const dim3 grid((unsigned)((nwt + 7) / 8 * 8 * p.groups));
-    if (p.groups > 1) launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, false>, grid, dim3(kWdThreads), st, a);
-    else launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, true>, grid, dim3(kWdThreads), st, a);
+    if (p.groups > 1) launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, false, AHEAD>, grid, dim3(kWdThreads), st, a);
+    else launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, true, AHEAD>, grid, dim3(kWdThreads), st, a);
 }
 
-template <int TOK, int P, int NB, int D>
+template <int TOK, int P, int NB, int D, bool AHEAD>
 void launch_wide_gate_moe(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     const int nwt = (p.ntiles + NB / kBxRows - 1) / (NB / kBxRows);
-    launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, true, true>, dim3((unsigned)(p.groups * nwt)), dim3(kWdThreads),
+    launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, true, true, AHEAD>, dim3((unsigned)(p.groups * nwt)), dim3(kWdThreads),
            st, a);
 }
 
-template <int TOK, int P, int CW, int WC, int KS, int D, int MAXT>
+template <int TOK, int P, int CW, int WC, int KS, int D, int MAXT, bool AHEAD>
 void launch_wide_down_cw(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     const int share = a.topk ? 1 : p.vpe;
     const dim3 dgrid((unsigned)((p.groups / share * p.nchunks + 7) / 8 * 8 * p.nslices * share));
-    if (share > 1) launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, false>, dgrid, dim3(kWdThreads), st, a);
-    else launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, true>, dgrid, dim3(kWdThreads), st, a);
+    if (share > 1) launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, false, AHEAD>, dgrid, dim3(kWdThreads), st, a);
+    else launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, true, AHEAD>, dgrid, dim3(kWdThreads), st, a);
 }
 
 }  // namespace
@@ -679,18 +741,19 @@ void launch_wide_prep(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
 // and bx_down 58.0 / 28.8), 64 tokens 55 / 34.6 (85.8 / 42.7), 256 tokens
 // 113 / 67 (four passes of 64: 327 / 168).
 void launch_wide_gate_up(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
-    if (p.parts == 3 && a.topk) launch_wide_gate_moe<64, 3, 128, 1>(p, a, st);
-    else if (p.parts == 3) launch_wide_gate<64, 3, 64, 1>(p, a, st);
-    else if (p.tok == 128) launch_wide_gate<128, 2, 128, 2>(p, a, st);
-    else if (p.tok == 64) launch_wide_gate<64, 2, 64, 2>(p, a, st);
-    else launch_wide_gate<32, 2, 64, 4>(p, a, st);
+    if (p.parts == 3 && a.topk) launch_wide_gate_moe<64, 3, 128, 1, false>(p, a, st);
+    else if (p.parts == 3) launch_wide_gate<64, 3, 64, 1, true>(p, a, st);
+    else if (p.tok == 128 && p.groups * p.ntiles < 4 * 192) launch_wide_gate<128, 2, 64, 2, true>(p, a, st);
+    else if (p.tok == 128) launch_wide_gate<128, 2, 128, 2, true>(p, a, st);
+    else if (p.tok == 64) launch_wide_gate<64, 2, 64, 2, true>(p, a, st);
+    else launch_wide_gate<32, 2, 64, 4, false>(p, a, st);
 }
 
 void launch_wide_down(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
-    if (p.parts == 3) launch_wide_down_cw<64, 3, 256, 4, 1, 2, wd_down_tiles(64, 3)>(p, a, st);
-    else if (p.tok == 128) launch_wide_down_cw<128, 2, 256, 4, 2, 1, wd_down_tiles(128, 2)>(p, a, st);
-    else if (p.tok == 64) launch_wide_down_cw<64, 2, 128, 4, 2, 1, wd_down_tiles(64, 2)>(p, a, st);
-    else launch_wide_down_cw<32, 2, 128, 8, 2, 1, wd_down_tiles(32, 2)>(p, a, st);
+    if (p.parts == 3) launch_wide_down_cw<64, 3, 256, 4, 1, 2, wd_down_tiles(64, 3), true>(p, a, st);
+    else if (p.tok == 128) launch_wide_down_cw<128, 2, 256, 4, 2, 1, wd_down_tiles(128, 2), true>(p, a, st);
+    else if (p.tok == 64) launch_wide_down_cw<64, 2, 128, 4, 2, 1, wd_down_tiles(64, 2), true>(p, a, st);
+    else launch_wide_down_cw<32, 2, 128, 8, 2, 1, wd_down_tiles(32, 2), true>(p, a, st);
 }
 
 }  // namespace ts

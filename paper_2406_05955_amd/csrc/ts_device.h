@@ -165,6 +165,15 @@ __device__ __forceinline__ void split_hi_lo(float x, uint32_t &hi, uint32_t &lo)
     lo = bf16_bits(x - __uint_as_float(hi << 16));
 }
 
+// 16-byte piece of part p of chunk c (8 values) in a token's row of the
+// router's x split.  Two parts: a chunk's parts together.  Three parts: the
+// four chunks of a 32-wide k-step together, part by part, since the wide
+// kernel's gather takes one part of a k-step from 16 tokens per instruction
+// (64 contiguous bytes of a token, not four pieces 48 bytes apart).
+__device__ __forceinline__ int xs_pos(int c, int p, int parts) {
+    return parts == 3 ? ((c >> 2) * 3 + p) * 4 + (c & 3) : 2 * c + p;
+}
+
 // The open-gate threshold and the Combined activation of a neuron whose
 // gate passed it: act 0 = dReLU (Eq. drelu), 1 = gate-only ReLU with
 // threshold tau.

@@ -1798,8 +1798,8 @@ __global__ __launch_bounds__(256) void ffn_union_count(const int32_t *__restrict
 // wave 0 takes the softmax, the top-k and the renormalised weights
 // (route_wave).  With xs set (bf16 weights, the batched path), the block
 // also writes its token's x as xs_parts (2 or 3) bf16 parts for the matrix
-// cores: row t of xs holds xs_chunks chunks of 8 values (k = 8 c .. 8 c + 7),
-// each 16 xs_parts bytes (the 8 high parts, then the next parts), zero past H.
+// cores: row t of xs holds xs_chunks chunks of 8 values (k = 8 c .. 8 c + 7)
+// in xs_parts pieces of 16 bytes, at xs_pos, zero past H.
 template <typename WT, int NC>
 __global__ __launch_bounds__(256) void moe_router(const float *__restrict__ x, const WT *__restrict__ wr, int H,
                                                   int E, int K, int32_t *__restrict__ topk_idx,
@@ -1832,12 +1832,12 @@ __global__ __launch_bounds__(256) void moe_router(const float *__restrict__ x, c
                             const uint32_t b1 = xs_parts == 3 ? bf16_take<3>(r[2 * e + 1]) : bf16_take<2>(r[2 * e + 1]);
                             o[e] = b0 | (b1 << 16);
                         }
-                        row[xs_parts * c + p] = u32x4{o[0], o[1], o[2], o[3]};
+                        row[xs_pos(c, p, xs_parts)] = u32x4{o[0], o[1], o[2], o[3]};
                     }
                 }
             }
-            for (int c = nch * xs_parts + (int)threadIdx.x; c < xs_chunks * xs_parts; c += 256)
-                row[c] = u32x4{0u, 0u, 0u, 0u};
+            for (int c = nch + (int)threadIdx.x; c < xs_chunks; c += 256)
+                for (int p = 0; p < xs_parts; ++p) row[xs_pos(c, p, xs_parts)] = u32x4{0u, 0u, 0u, 0u};
         }
     }
     // every block reads all router rows: cached loads, and the blocks that

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
         aoff[j] = 2u * (uint32_t)min(r0 + row, a.I - 1) * (uint32_t)H + 16u * (uint32_t)ac;
     }
     // x chunks: linear in the group's fragments, or gathered from the
-    // token-major split (16 P bytes per 8 values of a token)
+    // token-major split (pieces at xs_pos)
     const u32x4 *xb = reinterpret_cast<const u32x4 *>(a.xhl) + (size_t)g * (a.hpad / 32) * NX * 64;
     const __amdgpu_buffer_rsrc_t rx =
         GATHER ? make_rsrc(a.xtok, (uint32_t)a.B * (uint32_t)a.xchunks * 16u * P)
@@ -258,8 +258,7 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
                 const int l = idx & 63, f = (idx >> 6) % NX, s = (idx >> 6) / NX;
                 const int tk = s_tok[16 * (f / P) + (l & 15)];
                 if (tk >= 0)
-                    xoff[j] = (uint32_t)tk * (uint32_t)a.xchunks * (16u * P) +
-                              (uint32_t)(4 * s + (l >> 4)) * (16u * P) + 16u * (uint32_t)(f % P);
+                    xoff[j] = ((uint32_t)tk * (uint32_t)a.xchunks * P + (uint32_t)xs_pos(4 * s + (l >> 4), f % P, P)) * 16u;
             } else {
                 if (16 * ((idx >> 6) % NX / P) < ng) xoff[j] = 16u * (uint32_t)idx;
             }

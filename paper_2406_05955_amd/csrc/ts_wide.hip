@@ -267,8 +267,22 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
     constexpr uint32_t XSTEP = GATHER ? KS * 4 * 16 * P : XCH * 16;  // bytes per stage
 
     u32x4 ra[D][NA], rb[D][NXL];
-    auto issue = [&](int d, int st) {
-        const bool kin = st * 64 + 8 * ac < H;
+    // MoE, rows of 8 KB and more: every workgroup starts at another fold of
+    // the hidden dimension.  In step, all would read the same 128-byte column
+    // of rows that far apart, and how many memory channels that meets depends
+    // on where the weights lie: Mixtral shape, 128 tokens, 402 to 475 us over
+    // several allocations, 398 to 400 with it.  Rows of 4 KB: 102 to 109 us
+    // without, 109 with.  The FFN (one weight set) gained nothing: 32 tokens
+    // 43.2 / 45.8 us, 256 tokens 102.4 / 104.9.
+    const int rot = GATHER && nst >= 64 ? 8 * ((int)(blockIdx.x / 8) % (nst / 8)) : 0;
+    auto issue = [&](int d, int lst) {
+        int st = lst;
+        if constexpr (GATHER) {
+            st += rot;
+            st -= st >= nst ? nst : 0;
+        }
+        // (a stage past the last one loads nothing)
+        const bool kin = (!GATHER || lst < nst) && st * 64 + 8 * ac < H;
 #pragma unroll
         for (int j = 0; j < NA; ++j)
             ra[d][j] = wd_ld<STREAM>(j < NA / 2 ? rwg : rwu, kin ? aoff[j] + 128u * (uint32_t)st : kWdOob);

@@ -51,7 +51,8 @@ def test_wide_ffn(B, H, I):
 
 @pytest.mark.parametrize("B,H,I,E,K,skew", [(65, 512, 700, 8, 2, False), (128, 1032, 130, 4, 2, False),
                                             (130, 256, 65, 8, 1, True), (256, 264, 300, 64, 4, False),
-                                            (100, 128, 33, 1, 1, False)])
+                                            (100, 128, 33, 1, 1, False),
+                                            (66, 4096, 130, 4, 2, False), (70, 4104, 65, 2, 1, False)])
 def test_wide_moe(B, H, I, E, K, skew):
     """skew: every token routed to expert 0, which then takes several groups."""
     m = synth.make_moe(B, H, I, E, K, gate_bias=-0.84, dtype=synth.BF16, seed=[72, B, H, I, E, K])

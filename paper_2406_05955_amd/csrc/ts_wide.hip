@@ -750,9 +750,16 @@ void launch_wide_prep(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
 }
 
 // Stages in flight, rows and columns per workgroup as measured on the
-// Mistral shape (gate + up / down in us): 32 tokens 45.0 / 25.2 (bx_gate_up64
-// and bx_down 58.0 / 28.8), 64 tokens 55 / 34.6 (85.8 / 42.7), 256 tokens
-// 113 / 67 (four passes of 64: 327 / 168).
+// Mistral shape (gate + up / down in us): 32 tokens 43 / 25.5 (bx_gate_up64
+// and bx_down 58.0 / 28.8), 64 tokens 52 / 33 (85.8 / 42.7), 256 tokens
+// 102 / 64 (four passes of 64: 327 / 168).  More stages in flight changed
+// nothing (gate + up) or lost (down, two stages: 41 at 64 tokens, 79 at 256).
+// At 128 slots a workgroup takes 64 neurons where 128 leave fewer than 192
+// workgroups for the 256 compute units: 128 tokens, 110 -> 69 us (two groups,
+// 224 workgroups of 128 neurons: each x stage serves twice the weights).
+// Operands a k-step ahead (the last flag): 256 tokens 115 -> 102 us; not at
+// 32 slots (131 registers leave one workgroup per unit instead of two) nor in
+// the MoE form (spills).
 void launch_wide_gate_up(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     if (p.parts == 3 && a.topk) launch_wide_gate_moe<64, 3, 128, 1, false>(p, a, st);
     else if (p.parts == 3) launch_wide_gate<64, 3, 64, 1, true>(p, a, st);

@@ -18,7 +18,8 @@ ts = pytest.importorskip("paper_2406_05955_amd.binding") if torch.cuda.is_availa
 
 
 @pytest.mark.parametrize("B,H,I", [(17, 8, 1), (32, 1000, 65), (33, 4096, 130), (64, 264, 1500), (65, 512, 700),
-                                   (128, 1032, 33), (129, 256, 513), (200, 2048, 300), (256, 520, 2100)])
+                                   (128, 1032, 33), (129, 256, 513), (200, 2048, 300), (256, 520, 2100),
+                                   (129, 136, 12289), (256, 64, 12300)])
 def test_wide_ffn(B, H, I):
     inp = synth.make_ffn(B, H, I, gate_bias=-0.84, dtype=synth.BF16, seed=[71, B, H, I])
     ref = oracle.ffn(inp.x, inp.w_gate, inp.w_up, inp.w_down_t, inp.dtype)

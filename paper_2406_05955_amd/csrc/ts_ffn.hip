@@ -155,6 +155,11 @@ struct SlotArgs {
 // lanes (max and arg-max are exact; the softmax sum is taken from lane 0),
 // and nothing is indexed at run time, so no private memory is used.  Lane
 // k < K ends with the expert of rank k in *idx and its weight in *w.
+//
+// The K experts are always distinct: the batched routes size an expert's
+// groups for each token once.  With a non-finite logit every probability is
+// NaN, which no comparison orders, so a NaN is chosen as 0 (the K lowest
+// experts; the weights stay NaN as 0 / 0).
 __device__ inline void route_wave(const float *logit, int E, int K, int lane, int *idx, float *w) {
     const bool in = lane < E;
     const float l = in ? logit[lane] : -INFINITY;
@@ -173,7 +178,7 @@ __device__ inline void route_wave(const float *logit, int E, int K, int lane, in
 #pragma unroll
     for (int k = 0; k < kMaxTopK; ++k) {
         if (k < K) {
-            float v = (in && !taken) ? p : -1.f;  // probabilities are >= 0
+            float v = (in && !taken) ? (p >= 0.f ? p : 0.f) : -1.f;  // probabilities are >= 0, or NaN
             int bi = lane;
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1) {

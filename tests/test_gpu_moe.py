@@ -109,3 +109,32 @@ def test_moe_long_down_lists(I, dense):
     a third, one-tile list; the sparse layer at the same shapes alongside."""
     m = synth.make_moe(64, 256, I, 8, 2, gate_bias=-1.5548, dtype=synth.BF16, seed=[13, I])
     check_moe(m, dense=dense)
+
+
+@pytest.mark.parametrize("dtype,B,H,I,E,K,every", [(synth.BF16, 130, 520, 1205, 2, 2, 1),
+                                                   (synth.BF16, 130, 520, 1205, 2, 2, 3),
+                                                   (synth.BF16, 40, 264, 300, 4, 4, 1),
+                                                   (synth.F32, 40, 128, 3300, 2, 2, 1),
+                                                   (synth.BF16, 1, 264, 300, 8, 2, 1)])
+def test_moe_non_finite_tokens(dtype, B, H, I, E, K, every):
+    """Tokens whose router logits are NaN still take K distinct experts: an
+    expert's groups have room for each token once, so one expert drawn twice
+    by enough tokens (B K pairs against ceil(B / slots) groups: 260 against
+    192, 160 against 64, 80 against 64) would leave pairs without a slot.
+    Their outputs are NaN; the other tokens' are what they are without them."""
+    m = synth.make_moe(B, H, I, E, K, gate_bias=-0.84, dtype=dtype, seed=[74, B, E, K])
+    ref = oracle.moe(m.x, m.w_router, m.w_gate, m.w_up, m.w_down_t, m.dtype, K)
+    bad = np.arange(0, B, every)
+    x = m.x.copy()
+    x[bad, 3] = np.nan
+    args = [to_dev(m.w_router), to_dev(m.w_gate), to_dev(m.w_up), to_dev(m.w_down_t)]
+    for dense in (False, True):
+        out, idx, w = ts.moe_sparse(to_dev(x), *args, K, dense=dense)[:3]
+        torch.cuda.synchronize()
+        out, idx, w = out.cpu().numpy(), idx.cpu().numpy(), w.cpu().numpy()
+        assert (idx[bad] == np.arange(K)).all()
+        assert np.isnan(w[bad]).all() and np.isnan(out[bad]).all()
+        good = [t for t in range(B) if t % every and not near_tie(ref.probs[t], K)]
+        if good:
+            assert idx[good].tolist() == ref.topk_idx[good].tolist()
+            assert rel_l2(out[good], ref.y[good]) <= TIGHT_BATCH

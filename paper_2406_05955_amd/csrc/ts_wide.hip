@@ -101,6 +101,23 @@ __device__ __forceinline__ void wd_spread() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// The same for a half stage of N operand fragments with G matrix
+// instructions each: the reads follow the instructions, so a fragment's
+// register is free for the next k-step's by the time that is read.
+template <int R, int W, int N, int G, int I = 0>
+__device__ __forceinline__ void wd_roll() {
+    if constexpr (I < N) {
+        constexpr int READS = (I + 1) * R / N - I * R / N;
+        constexpr int WRITES = 2 * I < N ? 0 : (2 * I + 2 - N) * W / N - (2 * I - N) * W / N;  // the later half
+        __builtin_amdgcn_sched_group_barrier(0x008, G, 0);
+        if constexpr (READS > 0) __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+        if constexpr (WRITES > 0) __builtin_amdgcn_sched_group_barrier(0x200, WRITES, 0);
+        wd_roll<R, W, N, G, I + 1>();
+    } else {
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 }  // namespace
 
 // x of every group's token slots as MFMA operand fragments in P parts (the
@@ -156,7 +173,13 @@ __global__ __launch_bounds__(256) void wd_prep(BxArgs a) {
 // (off where several groups share a weight set: the second group's read of a
 // tile then hits in L2, since both run on one XCD).
 // QSPLIT: the sums of the hidden dimension's quarters are added in
-// bx_gate_up's order, (q0 + q1) + (q2 + q3): the same bits.
+// bx_gate_up's order, (q0 + q1) + (q2 + q3): the same bits.  QSEQ (128
+// slots): one after another, which holds one total besides the running sums.
+// A single chain over the hidden dimension rounds more: error against 64 bits
+// at hidden 4096 / 8192 4.92e-6 / 5.00e-6, in quarters 4.88e-6 / 4.91e-6 (as
+// the passes of 64 tokens), for 103 -> 107 us at 256 tokens of the Mistral
+// shape, 69.5 -> 71.5 at 128.  ROLL: the totals leave room for one register
+// slot of x fragments, not two (wd_roll).
 template <int TOK, int P, int NB, int D, bool GATHER, bool STREAM, bool AHEAD>
 __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
     constexpr int KS = 2;                       // 32-wide k-steps per stage
@@ -168,6 +191,7 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
     constexpr int NT = TOK / 32;                // token n-tiles per wave
     constexpr int NW = NB / kBxRows;            // 32-row tiles per workgroup
     constexpr bool QSPLIT = TOK <= 64 && P == 2;
+    constexpr bool QSEQ = TOK > 64, ROLL = QSEQ && NB == 128;
     constexpr int ABUF = 2 * NB * 8, BBUF = XCH;  // 16-byte units per LDS buffer
     constexpr int SH = NB * P * TOK / 8;          // 16-byte units of the Combined staging
     constexpr int LDS = 2 * (ABUF + BBUF) > SH ? 2 * (ABUF + BBUF) : SH;
@@ -358,7 +382,7 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
     auto steps_n = [&](int s0, int s1, auto nac) {
         constexpr int NACT = decltype(nac)::value;
         constexpr int R = NACT ? 2 * MN + NACT * P : 0, M = 2 * MN * NACT * P;  // (of a k-step)
-        if (AHEAD && s0 == 0) load(0, 0, nac);
+        if (AHEAD && (QSEQ || s0 == 0)) load(0, 0, nac);
         for (int st = s0; st < s1; st += U) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -368,13 +392,15 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
                 if constexpr (!AHEAD) contract(1, nac);
                 stash((u + 1) % D, (u + 1) & 1);
                 issue((u + 1) % D, st + u + 1 + D);
-                if constexpr (AHEAD) wd_spread<R, NA + NXL, M>();
+                if constexpr (AHEAD && ROLL && NACT > 0) wd_roll<R, NA + NXL, NACT * P, 2 * MN>();
+                else if constexpr (AHEAD) wd_spread<R, NA + NXL, M>();
                 wd_barrier();
                 if constexpr (AHEAD) {
                     __builtin_amdgcn_sched_barrier(0);
                     load((u + 1) & 1, 0, nac);
                     contract(1, nac);
-                    wd_spread<R, 0, M>();
+                    if constexpr (ROLL && NACT > 0) wd_roll<R, 0, NACT * P, 2 * MN>();
+                    else wd_spread<R, 0, M>();
                 }
             }
         }
@@ -434,7 +460,23 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
                 }
         }
     } else {
-        steps(0, nst);
+        f32x4 tg[MN][NT], tu[MN][NT];
+#pragma unroll
+        for (int m = 0; m < MN; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) tg[m][n] = tu[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < 4; ++q) {
+            clear();
+            steps(q * (nst / 4), (q + 1) * (nst / 4));
+#pragma unroll
+            for (int m = 0; m < MN; ++m)
+#pragma unroll
+                for (int n = 0; n < NT; ++n) tg[m][n] += cg[m][n], tu[m][n] += cu[m][n];
+        }
+#pragma unroll
+        for (int m = 0; m < MN; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) cg[m][n] = tg[m][n], cu[m][n] = tu[m][n];
     }
 
     // ---- open gates, active rows: lane (lm, lq), register i holds neuron
@@ -752,11 +794,14 @@ void launch_wide_prep(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
 // Stages in flight, rows and columns per workgroup as measured on the
 // Mistral shape (gate + up / down in us): 32 tokens 43 / 25.5 (bx_gate_up64
 // and bx_down 58.0 / 28.8), 64 tokens 52 / 33 (85.8 / 42.7), 256 tokens
-// 102 / 64 (four passes of 64: 327 / 168).  More stages in flight changed
-// nothing (gate + up) or lost (down, two stages: 41 at 64 tokens, 79 at 256).
+// 107 / 65 (four passes of 64: 327 / 168).  More stages in flight changed
+// nothing (gate + up) or lost (down, two stages: 41 at 64 tokens, 79 at 256);
+// with 128 neurons and 128 slots a second stage does not fit the registers
+// (spills in the loop: 157 us).
 // At 128 slots a workgroup takes 64 neurons where 128 leave fewer than 192
-// workgroups for the 256 compute units: 128 tokens, 110 -> 69 us (two groups,
-// 224 workgroups of 128 neurons: each x stage serves twice the weights).
+// workgroups for the 256 compute units: 128 tokens, 110 -> 71 us (two groups,
+// 224 workgroups of 128 neurons: each x stage serves twice the weights, 107
+// us against 128 with 64).
 // Operands a k-step ahead (the last flag): 256 tokens 115 -> 102 us; not at
 // 32 slots (131 registers leave one workgroup per unit instead of two) nor in
 // the MoE form (spills).
@@ -764,7 +809,7 @@ void launch_wide_gate_up(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     if (p.parts == 3 && a.topk) launch_wide_gate_moe<64, 3, 128, 1, false>(p, a, st);
     else if (p.parts == 3) launch_wide_gate<64, 3, 64, 1, true>(p, a, st);
     else if (p.tok == 128 && p.groups * p.ntiles < 4 * 192) launch_wide_gate<128, 2, 64, 2, true>(p, a, st);
-    else if (p.tok == 128) launch_wide_gate<128, 2, 128, 2, true>(p, a, st);
+    else if (p.tok == 128) launch_wide_gate<128, 2, 128, 1, true>(p, a, st);
     else if (p.tok == 64) launch_wide_gate<64, 2, 64, 2, true>(p, a, st);
     else launch_wide_gate<32, 2, 64, 4, false>(p, a, st);
 }

@@ -1,0 +1,78 @@
+"""The batched routes' error against 64 bits beside that of the kernels they
+stand in for (a knob takes the call there): fp32-exact routes against the
+single-token kernels, the wide kernels against passes of 64 tokens.  Each
+shape makes one chain of roundings the long one: the gate and up sums over
+the hidden dimension, the down sums over a chunk's rows, the sums over the
+chunks.
+
+Bounds: the errors' norms are those of some thousands of independent
+roundings (tokens x active neurons), so either scatters by 1 to 2% of itself;
+3% between exact routes.  With two bf16 parts the same split rounds both
+results, so what differs is the sums alone: 0.5%."""
+import pytest
+import torch
+
+from gpu_util import to_dev
+from paper_2406_05955_amd import synth
+from test_gpu_exact_batch import launches
+
+pytestmark = pytest.mark.gpu
+
+ts = pytest.importorskip("paper_2406_05955_amd.binding") if torch.cuda.is_available() else None
+
+
+def as64(w, dtype):
+    return (w.view(torch.bfloat16) if dtype == synth.BF16 else w).double()
+
+
+def exact(m, args, act, tau):
+    x, wr, wg, wu, wd = args
+    x = x.double()
+    y = torch.zeros_like(x)
+    p = torch.softmax(x @ as64(wr, m.dtype).T, dim=1)
+    pw, sel = torch.sort(p, dim=1, descending=True, stable=True)
+    pw = pw[:, :m.top_k] / pw[:, :m.top_k].sum(dim=1, keepdim=True)
+    for e in range(wg.shape[0]):
+        t, k = torch.nonzero(sel[:, :m.top_k] == e, as_tuple=True)
+        g, u = x[t] @ as64(wg[e], m.dtype).T, x[t] @ as64(wu[e], m.dtype).T
+        h = (g - tau).clamp(min=0) * u if act else g.clamp(min=0) * u.clamp(min=0)
+        y.index_add_(0, t, (h @ as64(wd[e], m.dtype)) * pw[t, k][:, None])
+    return y
+
+
+@pytest.mark.parametrize("entry,dtype,B,H,I,E,K,bias,tune,bound", [
+    ("ffn", synth.BF16, 128, 8192, 300, 1, 1, -0.84, {}, 1.005),             # gate + up, 128 slots, 64 neurons
+    ("ffn", synth.BF16, 256, 8192, 12300, 1, 1, -0.84, {}, 1.005),           # and 128 neurons per workgroup
+])
+def test_no_more_rounding(entry, dtype, B, H, I, E, K, bias, tune, bound):
+    m = synth.make_moe(B, H, I, E, K, gate_bias=bias, dtype=dtype, seed=[91, B, H, I])
+    args = tuple(to_dev(a) for a in (m.x, m.w_router, m.w_gate, m.w_up, m.w_down_t))
+    x, wr, wg, wu, wd = args
+    tau = 0.25 if entry == "act" else 0.0
+
+    def call():
+        if entry == "ffn":
+            return ts.ffn_sparse(x, wg[0], wu[0], wd[0])
+        if entry == "act":
+            return ts.ffn_sparse_act(x, wg[0], wu[0], wd[0], ts.TS_ACT_RELU_GATE, tau)
+        return ts.moe_sparse(x, wr, wg, wu, wd, K)[0]
+
+    ref = exact(m, args, entry == "act", tau)
+    knob = "bx_wide" if dtype == synth.BF16 and entry == "ffn" else "batch_path"
+    try:
+        for k, v in tune.items():
+            ts.tune_set(k, v)
+        got = call()
+        assert launches(call, "batch_down") == 1  # (the route under test)
+        for k in tune:
+            ts.tune_set(k, 0)
+        ts.tune_set(knob, 1)
+        old = call()
+        torch.cuda.synchronize()
+    finally:
+        ts.tune_set(knob, 0)
+        for k in tune:
+            ts.tune_set(k, 0)
+    e_new, e_old = ((o.double() - ref).norm().item() / ref.norm().item() for o in (got, old))
+    print(f"error {e_new:.3e}, before {e_old:.3e}, ratio {e_new / e_old:.4f}")
+    assert 0 < e_new <= bound * e_old

@@ -43,6 +43,8 @@ def exact(m, args, act, tau):
 @pytest.mark.parametrize("entry,dtype,B,H,I,E,K,bias,tune,bound", [
     ("ffn", synth.BF16, 128, 8192, 300, 1, 1, -0.84, {}, 1.005),             # gate + up, 128 slots, 64 neurons
     ("ffn", synth.BF16, 256, 8192, 12300, 1, 1, -0.84, {}, 1.005),           # and 128 neurons per workgroup
+    ("act", synth.BF16, 18, 1024, 7500, 1, 1, -1.55, {}, 1.03),              # three parts: gate + up
+    ("moe", synth.BF16, 70, 1024, 3000, 4, 2, -1.55, {}, 1.03),
 ])
 def test_no_more_rounding(entry, dtype, B, H, I, E, K, bias, tune, bound):
     m = synth.make_moe(B, H, I, E, K, gate_bias=bias, dtype=dtype, seed=[91, B, H, I])

@@ -690,37 +690,59 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_down(BxArgs a) {
                     v = mfma_bf16(wf[slot][c], hf[slot][P * n + p], v);
                 }
     };
-    constexpr int U = D > 2 ? D : 2;
+    // The sums are folded into totals every FB blocks (256 listed rows): a
+    // chain of roundings spans those, not the whole chunk (two parts, 256
+    // tokens: 4.88e-6 instead of 4.93e-6; three parts, a chunk of 7000 active
+    // rows: 1.8e-7 instead of 4.2e-7, the single-token kernels' 1.8e-7).  It
+    // costs 2 us of 65 at 128 slots and nothing elsewhere.
+    constexpr int U = D > 2 ? D : 2, FB = 8 / KS;
+    static_assert(FB % U == 0, "whole rounds between folds");
+    f32x4 tot[NC][NT];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) tot[c][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto blocks = [&](auto nac) {
         constexpr int NACT = decltype(nac)::value;
         constexpr int R = NACT ? 2 * (NC + NACT * P) : 0, M = NC * NACT * P;  // (of a k-step)
+        auto spread = [&]() {
+            if constexpr (TOK == 128 && NACT > 0) wd_roll<R, 0, NACT * P, NC>();
+            else wd_spread<R, 0, M>();
+        };
         if constexpr (AHEAD) load(0, 0, 0, nac);
-        for (int b = 0; b < nblk; b += U) {
+        for (int b0 = 0; b0 < nblk; b0 += FB) {
+            const int b1 = min(nblk, b0 + FB);
+            for (int b = b0; b < b1; b += U) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (b + u < nblk) {  // uniform over the workgroup
-                    if constexpr (AHEAD && KS == 2) {
-                        load(u & 1, 1, 1, nac);
-                        contract(0, nac);
-                        wd_spread<R, 0, M>();
-                    } else if constexpr (!AHEAD) {
+                for (int u = 0; u < U; ++u) {
+                    if (b + u < nblk) {  // uniform over the workgroup
+                        if constexpr (AHEAD && KS == 2) {
+                            load(u & 1, 1, 1, nac);
+                            contract(0, nac);
+                            spread();
+                        } else if constexpr (!AHEAD) {
 #pragma unroll
-                        for (int s = 0; s < KS; ++s) {
-                            load(u & 1, s, s, nac);
-                            contract(s, nac);
+                            for (int s = 0; s < KS; ++s) {
+                                load(u & 1, s, s, nac);
+                                contract(s, nac);
+                            }
                         }
-                    }
-                    stash((u + 1) % D, (u + 1) & 1);
-                    issue((u + 1) % D, b + u + 1 + D);
-                    wd_barrier();
-                    if constexpr (AHEAD) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        load((u + 1) & 1, 0, KS == 2 ? 0 : (u + 1) & 1, nac);
-                        contract(KS == 2 ? 1 : u & 1, nac);
-                        wd_spread<R, 0, M>();
+                        stash((u + 1) % D, (u + 1) & 1);
+                        issue((u + 1) % D, b + u + 1 + D);
+                        wd_barrier();
+                        if constexpr (AHEAD) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            load((u + 1) & 1, 0, KS == 2 ? 0 : (u + 1) & 1, nac);
+                            contract(KS == 2 ? 1 : u & 1, nac);
+                            spread();
+                        }
                     }
                 }
             }
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int n = 0; n < NACT; ++n) tot[c][n] += acc[c][n], acc[c][n] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     };
     if (nblk > 0) {
@@ -746,7 +768,7 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_down(BxArgs a) {
             for (int c = 0; c < NC; ++c) {
                 const int col = col0 + 16 * (wc * NC + c) + 4 * lq;
                 if (col < H)
-                    *reinterpret_cast<f32x4 *>(prow + col) = LO ? acc[c][n] + accl[LO ? c : 0][LO ? n : 0] : acc[c][n];
+                    *reinterpret_cast<f32x4 *>(prow + col) = LO ? tot[c][n] + accl[LO ? c : 0][LO ? n : 0] : tot[c][n];
             }
         }
     }
@@ -797,7 +819,7 @@ void launch_wide_prep(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
 // Stages in flight, rows and columns per workgroup as measured on the
 // Mistral shape (gate + up / down in us): 32 tokens 43 / 25.5 (bx_gate_up64
 // and bx_down 58.0 / 28.8), 64 tokens 52 / 33 (85.8 / 42.7), 256 tokens
-// 107 / 65 (four passes of 64: 327 / 168).  More stages in flight changed
+// 107 / 67 (four passes of 64: 327 / 168).  More stages in flight changed
 // nothing (gate + up) or lost (down, two stages: 41 at 64 tokens, 79 at 256);
 // with 128 neurons and 128 slots a second stage does not fit the registers
 // (spills in the loop: 157 us).

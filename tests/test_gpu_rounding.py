@@ -43,6 +43,7 @@ def exact(m, args, act, tau):
 @pytest.mark.parametrize("entry,dtype,B,H,I,E,K,bias,tune,bound", [
     ("ffn", synth.BF16, 128, 8192, 300, 1, 1, -0.84, {}, 1.005),             # gate + up, 128 slots, 64 neurons
     ("ffn", synth.BF16, 256, 8192, 12300, 1, 1, -0.84, {}, 1.005),           # and 128 neurons per workgroup
+    ("moe", synth.BF16, 70, 256, 7000, 2, 2, 0.0, {"down_chunks": 1}, 1.03),  # down
     ("act", synth.BF16, 18, 1024, 7500, 1, 1, -1.55, {}, 1.03),              # three parts: gate + up
     ("moe", synth.BF16, 70, 1024, 3000, 4, 2, -1.55, {}, 1.03),
 ])

@@ -225,16 +225,43 @@ __device__ __forceinline__ void bx_kloop(const char *wbase, const uint32_t (&rof
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) part[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (S::F32) {
+                // four chains of C k-steps' products (4 C each), added in pairs
+                auto chains = [&](auto cn) {
+                    constexpr int C = decltype(cn)::value;
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
+                    for (int s = 0; s < KS; s += C)
 #pragma unroll
-                for (int f = 0; f < NX; ++f)
+                        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        f32x4 &c = part[mt][S::PACK ? 0 : f / S::P];
-                        if constexpr (S::F32) c += bx_mma<M>(av[mt][s], xv[d][f][s], f32x4{0.f, 0.f, 0.f, 0.f});
-                        else c = bx_mma<M>(av[mt][s], xv[d][f][s], c);
-                    }
+                            for (int mt = 0; mt < MT; ++mt) {
+                                f32x4 p[4];
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) p[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                                for (int h = 0; h < C; ++h)
+#pragma unroll
+                                    for (int j = 0; j < 4; ++j)
+                                        p[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                            __builtin_bit_cast(f32x4, av[mt][s + h])[j],
+                                            __builtin_bit_cast(f32x4, xv[d][nt][s + h])[j], p[j], 0, 0, 0);
+                                part[mt][nt] += (p[0] + p[1]) + (p[2] + p[3]);
+                            }
+                };
+                if (Hb < 4096) chains(std::integral_constant<int, 1>{});
+                else chains(std::integral_constant<int, 2>{});
+            } else {
+                // the lower parts' products first: what those round is small
+#pragma unroll
+                for (int f = NX - 1; f >= 0; --f)
+#pragma unroll
+                    for (int s = 0; s < KS; ++s)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) {
+                            f32x4 &c = part[mt][S::PACK ? 0 : f / S::P];
+                            c = mfma_bf16(av[mt][s], xv[d][f][s], c);
+                        }
+            }
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll

@@ -39,21 +39,6 @@ struct Bx {
     static constexpr int DD = 2;                    // down blocks in flight per wave (default)
 };
 
-// One k-step's product of a 16-row weight operand with a 16-column x operand
-// (fp32: the lane's four elements in four steps; the k order inside a k-step
-// is the same for both operands).
-template <int M>
-__device__ __forceinline__ f32x4 bx_mma(const u32x4 a, const u32x4 b, f32x4 c) {
-    if constexpr (M == kBxF32) {
-        const f32x4 af = __builtin_bit_cast(f32x4, a), bf = __builtin_bit_cast(f32x4, b);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) c = __builtin_amdgcn_mfma_f32_16x16x4f32(af[j], bf[j], c, 0, 0, 0);
-        return c;
-    } else {
-        return mfma_bf16(a, b, c);
-    }
-}
-
 // Part p (< P, run-time) of v, without a branch.
 template <int P>
 __device__ __forceinline__ uint32_t bf16_sel(float v, int p) {

@@ -46,6 +46,10 @@ def exact(m, args, act, tau):
     ("moe", synth.BF16, 70, 256, 7000, 2, 2, 0.0, {"down_chunks": 1}, 1.03),  # down
     ("act", synth.BF16, 18, 1024, 7500, 1, 1, -1.55, {}, 1.03),              # three parts: gate + up
     ("moe", synth.BF16, 70, 1024, 3000, 4, 2, -1.55, {}, 1.03),
+    ("act", synth.BF16, 16, 1024, 8300, 1, 1, -1.55, {}, 1.03),              # three parts, 16 slots
+    ("ffn", synth.F32, 16, 512, 8300, 1, 1, -1.55, {}, 1.03),                # fp32 matrix operations, 16 slots
+    ("ffn", synth.F32, 24, 512, 5500, 1, 1, -1.55, {}, 1.03),                # 32 slots
+    ("ffn", synth.F32, 24, 1024, 5500, 1, 1, -1.55, {}, 1.03),
 ])
 def test_no_more_rounding(entry, dtype, B, H, I, E, K, bias, tune, bound):
     m = synth.make_moe(B, H, I, E, K, gate_bias=bias, dtype=dtype, seed=[91, B, H, I])

@@ -1248,10 +1248,11 @@ __global__ __launch_bounds__(256, 2) void bx_down_f32(BxArgs a) {
 // out[t][:] = sum over routed ranks k (ascending) of w[t][k] times the sum
 // over chunks of the partial row of (group, slot) = tslot[t][k].  Block:
 // 256 columns (64 float4, one per lane) x 4 share groups (one per wave); a
-// thread adds shares grp, grp + 4, ... (share k * nchunks + c) in order, and
-// the four groups' sums are combined in a fixed order through LDS.  One
-// block per (256 columns, token): the shares are few (top_k x chunks), so a
-// wide block keeps the grid small.
+// thread adds shares grp, grp + 4, ... (share k * nchunks + c), four (up to 8
+// shares in all: two) loaded and added in pairs at a time, and the four
+// groups' sums are combined in a fixed order through LDS.  One block per (256
+// columns, token): the shares are few (top_k x chunks), so a wide block keeps
+// the grid small.
 __global__ __launch_bounds__(256) void bx_reduce(BxArgs a) {
     __shared__ f32x4 red[4][64];
     const int t = blockIdx.y;
@@ -1261,16 +1262,24 @@ __global__ __launch_bounds__(256) void bx_reduce(BxArgs a) {
     const int nq = a.H / 4;
     const int total = a.K * a.nchunks;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int p = grp; p < total; p += 4) {
-        const int k = p / a.nchunks, c = p % a.nchunks;
-        const int g = a.tslot[(t * a.K + k) * 2], s = a.tslot[(t * a.K + k) * 2 + 1];
-        const float w = a.topw ? a.topw[t * a.K + k] : 1.f;
-        const f32x4 v = ld_f32x4_masked(a.partial + (((size_t)g * a.bpad + s) * a.nchunks + c) * a.H, c4, nq);
-        acc.x = fmaf(w, v.x, acc.x);
-        acc.y = fmaf(w, v.y, acc.y);
-        acc.z = fmaf(w, v.z, acc.z);
-        acc.w = fmaf(w, v.w, acc.w);
-    }
+    auto add = [&](auto un) {
+        constexpr int U = decltype(un)::value;
+        for (int p0 = grp; p0 < total; p0 += 4 * U) {
+            f32x4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int p = min(p0 + 4 * u, total - 1);
+                const int k = p / a.nchunks, c = p % a.nchunks;
+                const int g = a.tslot[(t * a.K + k) * 2], s = a.tslot[(t * a.K + k) * 2 + 1];
+                const float w = a.topw ? a.topw[t * a.K + k] : 1.f;
+                const f32x4 r = ld_f32x4_masked(a.partial + (((size_t)g * a.bpad + s) * a.nchunks + c) * a.H, c4, nq);
+                v[u] = p0 + 4 * u < total ? w * r : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            acc += U == 4 ? (v[0] + v[1]) + (v[U - 2] + v[U - 1]) : v[0] + v[1];
+        }
+    };
+    if (total > 8) add(std::integral_constant<int, 4>{});
+    else add(std::integral_constant<int, 2>{});
     red[grp][q] = acc;
     __syncthreads();
     if (grp == 0 && c4 < nq)

@@ -50,6 +50,7 @@ def exact(m, args, act, tau):
     ("ffn", synth.F32, 16, 512, 8300, 1, 1, -1.55, {}, 1.03),                # fp32 matrix operations, 16 slots
     ("ffn", synth.F32, 24, 512, 5500, 1, 1, -1.55, {}, 1.03),                # 32 slots
     ("ffn", synth.F32, 24, 1024, 5500, 1, 1, -1.55, {}, 1.03),
+    ("ffn", synth.F32, 6, 512, 26000, 1, 1, 0.0, {"down_chunks": 400}, 1.03),  # the sums over the chunks
 ])
 def test_no_more_rounding(entry, dtype, B, H, I, E, K, bias, tune, bound):
     m = synth.make_moe(B, H, I, E, K, gate_bias=bias, dtype=dtype, seed=[91, B, H, I])

@@ -337,6 +337,10 @@ ts_status ts_probe_copy(const void *src, void *dst, size_t bytes, void *stream);
  *                0 default (the workgroup-tiled kernels where their plan
  *                fits the workspace), 1 = passes of up to 64 tokens on the
  *                other batched kernels (MoE: the single-token kernels)
+ *   "bx_exact"   batched kernels with fp32 products (fp32 weights,
+ *                TS_ACT_RELU_GATE, MoE layer above 64): 0 default (where
+ *                the weight readings that they save pay for their launches),
+ *                1 = wherever their plan fits the workspace
  *   "ffn_interleave" single-token kernels: 0 default (workgroup t takes
  *                neurons t, t + T, t + 2 T, ... of T workgroups per token,
  *                so the grid streams one narrow band of each matrix at a

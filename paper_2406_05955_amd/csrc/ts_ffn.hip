@@ -2331,11 +2331,13 @@ ts_status moe_impl(const float *x, const void *wr, const void *wg, const void *w
     float *rw = topk_w ? topk_w : ws_at<float>(ws, roff + align_up256((size_t)batch * K * sizeof(int32_t)));
     BatchPlan bp;
     const size_t estride = (size_t)inter * (size_t)hidden;
-    const bool batched = batch > 1 && tuned("batch_path") == 0 &&
-                         (plan_batch(batch, hidden, inter, E, K, dt, &bp) ||
-                          plan_wide_moe(batch, hidden, inter, E, K, dt, &bp) ||
-                          (dt == TS_F32 && tuned("ffn_path") == 0 && exact_pays(batch, hidden, inter, E, K, dt) &&
-                           plan_exact(batch, hidden, inter, E, K, dt, moe_route_offset(batch, hidden, inter, E, K, dt), &bp)));
+    const bool batched =
+        batch > 1 && tuned("batch_path") == 0 &&
+        (plan_batch(batch, hidden, inter, E, K, dt, &bp) ||
+         (exact_pays(batch, hidden, inter, E, K, dt) &&
+          (plan_wide_moe(batch, hidden, inter, E, K, dt, &bp) ||
+           (dt == TS_F32 && tuned("ffn_path") == 0 &&
+            plan_exact(batch, hidden, inter, E, K, dt, moe_route_offset(batch, hidden, inter, E, K, dt), &bp)))));
     // on the pipelined kernel each workgroup routes its own token (no router launch)
     const bool fold = !batched && slots_use_pipe(p, dense);
     // batched: the router also writes each token's x split for the matrix

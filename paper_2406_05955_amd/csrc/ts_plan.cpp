@@ -20,6 +20,7 @@ std::atomic<int> g_bx_vgroup{0};
 std::atomic<int> g_interleave{0};
 std::atomic<int> g_bx_xtok{0};
 std::atomic<int> g_bx_wide{0};
+std::atomic<int> g_bx_exact{0};
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 int esize(ts_dtype dt) { return dt == TS_F32 ? 4 : 2; }
@@ -42,6 +43,7 @@ int tuned(const char *key) {
     if (std::strcmp(key, "ffn_interleave") == 0) return g_interleave.load();
     if (std::strcmp(key, "bx_xtok") == 0) return g_bx_xtok.load();
     if (std::strcmp(key, "bx_wide") == 0) return g_bx_wide.load();
+    if (std::strcmp(key, "bx_exact") == 0) return g_bx_exact.load();
     return 0;
 }
 
@@ -322,14 +324,35 @@ bool plan_wide_moe(int batch, int hidden, int inter, int experts, int top_k, ts_
 
 // The single-token kernels read a weight set once per token (or routed
 // pair), the batched ones once: about one matrix's bytes per saved reading,
-// against two more launches and a longer chain.  Measured per layer, batched
-// against single-token: fp32 41 MB matrices, 2 tokens 30.5 / 28.6 us, 6
-// tokens 39 / 65; 3.7 MB, 4 tokens 21.6 / 17.5; bf16 (gate-only ReLU) 117 MB,
-// 2 tokens 57 / 43, 4 tokens 61 / 80; 8 MB, 16 tokens 30 / 24.
+// against two more launches and a longer chain (10 to 15 us).  What a saved
+// reading is worth depends on where it comes from: matrices below 32 MB stay
+// in the caches, and the second token of two streams beside the first.
+// Measured per layer, single-token time over batched (6 and 20% open gates),
+// at the bytes saved:
+//   fp32, matrices of 32 MB and more: 41 MB, 3 tokens (82 MB) 1.09 / 1.15;
+//     57 MB, 3 tokens (115) 1.37 / 1.33; 2 tokens: 82 MB 0.95, 117 MB 0.89 /
+//     0.91, 235 MB 1.30 / 1.25
+//   fp32, smaller: 4 MB, 32 tokens (115) 0.62 / 0.72; 14 MB, 8 (100) 0.66 /
+//     0.73; 20 MB, 12 (226) 0.95 / 1.04; 29 MB, 9 (230) 0.86 / 0.90; 10 MB,
+//     32 (316) 0.98 / 1.16; 20 MB, 16 (308) 1.27; 29 MB, 12 (316) 1.52
+//   bf16 (gate-only ReLU): 117 MB, 2 tokens (117) 0.75, 4 (352) 1.25; 20 MB,
+//     12 (226) 1.01 / 1.13, 17 (328) 0.99 / 1.15; 37 MB, 8 (258) 1.63 / 1.72
+//   MoE, fp32: 29 MB, 8 experts, 12 (118) 0.98, 4 experts, 8 (118) 0.77; 4 MB
+//     (170) 0.77, (207) 1.32; 41 MB, 8 experts, 12 (164) 0.89; 14 MB (286)
+//     1.31, (343) 1.29
+//   MoE, bf16 above 64 tokens: 1.8 MB, 2 experts, 65 (113) 0.56 / 0.66, 128
+//     (227) 0.96 / 1.17; 3.7 MB, 80 (289) 0.98 / 1.21; 3.7 MB, 128 (466) 1.23
 bool exact_pays(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt) {
+    if (g_bx_exact.load() == 1) return batch > 1;
     const long long saved = (long long)batch * top_k - experts;
-    const long long line = (dt == TS_F32 ? 64LL : 240LL) << 20;
-    return saved > 0 && saved * inter * hidden * esize(dt) >= line;
+    const long long matrix = (long long)inter * hidden * esize(dt);
+    long long line = 288LL << 20;
+    if (experts == 1 && dt == TS_BF16) {
+        line = 240LL << 20;
+    } else if (experts == 1 && matrix >= 32LL << 20) {
+        line = (saved == 1 ? 192LL : 76LL) << 20;
+    }
+    return saved > 0 && saved * matrix >= line;
 }
 
 bool plan_exact(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt, size_t limit, BatchPlan *p) {
@@ -540,6 +563,11 @@ ts_status ts_tune_set(const char *key, int value) {
     if (std::strcmp(key, "bx_wide") == 0) {
         if (value < 0 || value > 1) return TS_ERR_SHAPE;
         ts::g_bx_wide.store(value);
+        return TS_OK;
+    }
+    if (std::strcmp(key, "bx_exact") == 0) {
+        if (value < 0 || value > 1) return TS_ERR_SHAPE;
+        ts::g_bx_exact.store(value);
         return TS_OK;
     }
     return TS_ERR_SHAPE;

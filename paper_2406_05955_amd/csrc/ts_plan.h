@@ -151,8 +151,9 @@ constexpr int kWdMinTokens = 16;
 constexpr int kRowsMaxTokens = 8;  // fp32 row streams (ts_rows.hip): tokens whose x fits LDS
 
 // Batches through the fp32-exact modes: fp32 weights, and the activation
-// forms whose other route is the single-token kernels.  `limit`: workspace
-// bytes that the plan has to fit.
+// forms whose other route is the single-token kernels (exact_pays: and the
+// MoE layer above kBxMaxTokens).  `limit`: workspace bytes that the plan has
+// to fit.
 bool exact_pays(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt);
 bool plan_exact(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt, size_t limit, BatchPlan *p);
 

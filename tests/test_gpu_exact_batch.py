@@ -1,7 +1,7 @@
 """Parity of the fp32-exact batched kernels (fp32 weights; the gate-only ReLU
 over bf16 weights) against the fp64 oracle at the single-token kernels'
-tolerances, at shapes just past the size rule that selects them: the row
-streams (up to 8 fp32 tokens, 4 / 6 / 8 token variants, one and two segments
+tolerances, at small shapes (the "bx_exact" knob takes them there; the size
+rule has a test of its own): the row streams (up to 8 fp32 tokens, 4 / 6 / 8 token variants, one and two segments
 per row), the fp32 matrix-core kernels (16 and 32 slots, several groups),
 the three-part kernels (8 and 16 slots; 64 slots, several groups), hidden
 and inter ragged, the dense comparator, the report and a reused workspace
@@ -34,10 +34,17 @@ def launches(fn, kernel):
         ts.prof_reset()
 
 
+@pytest.fixture
+def exact_route():
+    ts.tune_set("bx_exact", 1)
+    yield
+    ts.tune_set("bx_exact", 0)
+
+
 @pytest.mark.parametrize("B,H,I,bias", [(2, 4096, 4101, -0.84), (4, 1500, 3757, -0.84), (5, 2052, 2085, 8.0),
                                         (6, 516, 6600, -0.84), (8, 4096, 600, 0.0), (9, 1032, 2105, -0.84),
                                         (16, 260, 4400, -1.5), (17, 516, 2047, -0.84), (33, 260, 2050, -0.84)])
-def test_exact_f32(B, H, I, bias):
+def test_exact_f32(exact_route, B, H, I, bias):
     inp = synth.make_ffn(B, H, I, gate_bias=bias, dtype=synth.F32, seed=[81, B, H, I])
     out, st, ref = check_ffn(inp)
     x, wg, wu, wd = ffn_inputs_to_dev(inp)
@@ -57,7 +64,7 @@ def test_exact_f32(B, H, I, bias):
                                              (16, 2056, 4085, synth.BF16, 0.44), (17, 2056, 3830, synth.BF16, 0.1),
                                              (65, 1032, 1910, synth.BF16, -0.3), (130, 520, 1877, synth.BF16, 0.1),
                                              (6, 2052, 2000, synth.F32, 0.25), (12, 1032, 1800, synth.F32, -0.2)])
-def test_exact_act(B, H, I, dtype, tau):
+def test_exact_act(exact_route, B, H, I, dtype, tau):
     """tau < 0 as well: a token slot past the batch must not open a gate."""
     inp = synth.make_ffn(B, H, I, gate_bias=-0.84, dtype=dtype, seed=[82, B, H, I])
     out, ref = check_act(inp, tau)
@@ -67,7 +74,7 @@ def test_exact_act(B, H, I, dtype, tau):
 
 
 @pytest.mark.parametrize("B,H,I,E,K", [(16, 516, 1205, 4, 2), (40, 260, 905, 8, 2), (40, 128, 3300, 2, 2)])
-def test_exact_moe_f32(B, H, I, E, K):
+def test_exact_moe_f32(exact_route, B, H, I, E, K):
     m = synth.make_moe(B, H, I, E, K, gate_bias=-0.84, dtype=synth.F32, seed=[83, B, H, I, E, K])
     check_moe(m)
     check_moe(m, dense=True)
@@ -75,7 +82,7 @@ def test_exact_moe_f32(B, H, I, E, K):
     assert launches(lambda: ts.moe_sparse(*args, K), "batch_down") == 1
 
 
-def test_exact_union_counts():
+def test_exact_union_counts(exact_route):
     """The union report of a single-group batch on this route."""
     inp = synth.make_ffn(6, 1032, 3400, gate_bias=-0.84, dtype=synth.F32, seed=84)
     ref = oracle.ffn(inp.x, inp.w_gate, inp.w_up, inp.w_down_t, inp.dtype)
@@ -89,7 +96,7 @@ def test_exact_union_counts():
 
 
 @pytest.mark.parametrize("entry,B", [("act", 8), ("act", 12), ("act", 40), ("moe", 130)])
-def test_exact_whole_fp32_range(entry, B):
+def test_exact_whole_fp32_range(exact_route, entry, B):
     """Values that three bf16 parts could lose: an infinity, a NaN whose
     payload is all ones, and one above the largest bf16 (whose first part must
     not round to infinity).  Every token of the batch gives what it gives
@@ -123,3 +130,28 @@ def test_exact_whole_fp32_range(entry, B):
         assert np.array_equal(got[t][~f], want[t][~f], equal_nan=True), t
         scale = np.abs(want[t][f]).max(initial=0.0)
         assert np.abs(got[t][f] / max(scale, 1e-30) - want[t][f] / max(scale, 1e-30)).max(initial=0.0) <= 1e-5, t
+
+
+@pytest.mark.parametrize("entry,dtype,B,H,I,E,K,batched", [
+    ("ffn", synth.F32, 2, 4096, 5003, 1, 1, False), ("ffn", synth.F32, 3, 4096, 5003, 1, 1, True),
+    ("ffn", synth.F32, 8, 1024, 3500, 1, 1, False), ("ffn", synth.F32, 32, 1024, 3500, 1, 1, True),
+    ("ffn", synth.F32, 32, 512, 1792, 1, 1, False), ("ffn", synth.F32, 6, 2052, 5003, 1, 1, True),
+    ("act", synth.BF16, 4, 2048, 5000, 1, 1, False), ("act", synth.BF16, 16, 2048, 5000, 1, 1, True),
+    ("moe", synth.F32, 16, 512, 1792, 8, 2, False), ("moe", synth.F32, 16, 1024, 3500, 4, 2, True),
+    ("moe", synth.BF16, 65, 512, 1792, 2, 1, False), ("moe", synth.BF16, 65, 1024, 3584, 4, 2, True)])
+def test_exact_size_rule(entry, dtype, B, H, I, E, K, batched):
+    """Either side of the line: a call that re-reads little from far keeps the
+    single-token kernels (and, batched or not, gives the same result)."""
+    m = synth.make_moe(B, H, I, E, K, gate_bias=-0.84, dtype=dtype, seed=[86, B, H, I, E])
+    x, wr, wg, wu, wd = (to_dev(a) for a in (m.x, m.w_router, m.w_gate, m.w_up, m.w_down_t))
+    call = {"ffn": lambda: ts.ffn_sparse(x, wg[0], wu[0], wd[0]),
+            "act": lambda: ts.ffn_sparse_act(x, wg[0], wu[0], wd[0], ts.TS_ACT_RELU_GATE, 0.1),
+            "moe": lambda: ts.moe_sparse(x, wr, wg, wu, wd, K)[0]}[entry]
+    assert launches(call, "batch_down") == (1 if batched else 0)
+    got = call()
+    ts.tune_set("batch_path", 1)
+    try:
+        want = call()
+    finally:
+        ts.tune_set("batch_path", 0)
+    assert rel_l2(got.cpu().numpy(), want.cpu().numpy().astype(np.float64)) <= 2e-6

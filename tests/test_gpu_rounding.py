@@ -47,8 +47,8 @@ def exact(m, args, act, tau):
     ("act", synth.BF16, 18, 1024, 7500, 1, 1, -1.55, {}, 1.03),              # three parts: gate + up
     ("moe", synth.BF16, 70, 1024, 3000, 4, 2, -1.55, {}, 1.03),
     ("act", synth.BF16, 16, 1024, 8300, 1, 1, -1.55, {}, 1.03),              # three parts, 16 slots
-    ("ffn", synth.F32, 16, 512, 8300, 1, 1, -1.55, {}, 1.03),                # fp32 matrix operations, 16 slots
-    ("ffn", synth.F32, 24, 512, 5500, 1, 1, -1.55, {}, 1.03),                # 32 slots
+    ("ffn", synth.F32, 16, 512, 8300, 1, 1, -1.55, {"bx_exact": 1}, 1.03),                # fp32 matrix operations, 16 slots
+    ("ffn", synth.F32, 24, 512, 5500, 1, 1, -1.55, {"bx_exact": 1}, 1.03),                # 32 slots
     ("ffn", synth.F32, 24, 1024, 5500, 1, 1, -1.55, {}, 1.03),
     ("ffn", synth.F32, 6, 512, 26000, 1, 1, 0.0, {"down_chunks": 400}, 1.03),  # the sums over the chunks
 ])

@@ -162,6 +162,9 @@ bool plan_exact(int batch, int hidden, int inter, int experts, int top_k, ts_dty
 constexpr int wd_down_tiles(int tok, int parts) { return tok <= 64 && parts == 3 ? 224 : 64; }
 // Output columns per down workgroup.
 constexpr int wd_slice_cols(int tok, int parts) { return tok > 64 || parts == 3 ? 256 : 128; }
+// Whether a weight set of an FFN call may have several groups (two parts: 32
+// and 64 slots serve batches that fit one; 128 and the three-part 64 serve any).
+constexpr bool wd_many_groups(int tok, int parts) { return tok > 64 || parts == 3; }
 bool plan_wide_ffn(int batch, int hidden, int inter, ts_dtype dt, BatchPlan *p);
 bool plan_wide_moe(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt, BatchPlan *p);
 

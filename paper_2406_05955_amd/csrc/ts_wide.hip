@@ -782,8 +782,13 @@ template <int TOK, int P, int NB, int D, bool AHEAD>
 void launch_wide_gate(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     const int nwt = (p.ntiles + NB / kBxRows - 1) / (NB / kBxRows);
     const dim3 grid((unsigned)((nwt + 7) / 8 * 8 * p.groups));
-    if (p.groups > 1) launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, false, AHEAD>, grid, dim3(kWdThreads), st, a);
-    else launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, true, AHEAD>, grid, dim3(kWdThreads), st, a);
+    if constexpr (wd_many_groups(TOK, P)) {
+        if (p.groups > 1) {
+            launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, false, AHEAD>, grid, dim3(kWdThreads), st, a);
+            return;
+        }
+    }
+    launch("batch_gate_up", wd_gate_up<TOK, P, NB, D, false, true, AHEAD>, grid, dim3(kWdThreads), st, a);
 }
 
 template <int TOK, int P, int NB, int D, bool AHEAD>
@@ -797,8 +802,13 @@ template <int TOK, int P, int CW, int WC, int KS, int D, int MAXT, bool AHEAD>
 void launch_wide_down_cw(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     const int share = a.topk ? 1 : p.vpe;
     const dim3 dgrid((unsigned)((p.groups / share * p.nchunks + 7) / 8 * 8 * p.nslices * share));
-    if (share > 1) launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, false, AHEAD>, dgrid, dim3(kWdThreads), st, a);
-    else launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, true, AHEAD>, dgrid, dim3(kWdThreads), st, a);
+    if constexpr (wd_many_groups(TOK, P)) {
+        if (share > 1) {
+            launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, false, AHEAD>, dgrid, dim3(kWdThreads), st, a);
+            return;
+        }
+    }
+    launch("batch_down", wd_down<TOK, P, CW, WC, KS, D, MAXT, true, AHEAD>, dgrid, dim3(kWdThreads), st, a);
 }
 
 }  // namespace

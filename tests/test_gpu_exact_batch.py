@@ -1,8 +1,9 @@
 """Parity of the fp32-exact batched kernels (fp32 weights; the gate-only ReLU
 over bf16 weights) against the fp64 oracle at the single-token kernels'
 tolerances, at small shapes (the "bx_exact" knob takes them there; the size
-rule has a test of its own): the row streams (up to 8 fp32 tokens, 4 / 6 / 8 token variants, one and two segments
-per row), the fp32 matrix-core kernels (16 and 32 slots, several groups),
+rule has a test of its own): the row streams (up to 8 fp32 tokens, 4 / 6 / 8
+token variants, one and two segments per row, one and two tiles per
+workgroup), the fp32 matrix-core kernels (16 and 32 slots, several groups),
 the three-part kernels (8 and 16 slots; 64 slots, several groups), hidden
 and inter ragged, the dense comparator, the report and a reused workspace
 full of NaN."""
@@ -43,7 +44,10 @@ def exact_route():
 
 @pytest.mark.parametrize("B,H,I,bias", [(2, 4096, 4101, -0.84), (4, 1500, 3757, -0.84), (5, 2052, 2085, 8.0),
                                         (6, 516, 6600, -0.84), (8, 4096, 600, 0.0), (9, 1032, 2105, -0.84),
-                                        (16, 260, 4400, -1.5), (17, 516, 2047, -0.84), (33, 260, 2050, -0.84)])
+                                        (16, 260, 4400, -1.5), (17, 516, 2047, -0.84), (33, 260, 2050, -0.84),
+                                        # row streams: two tiles per workgroup (the last with one of one
+                                        # row), two chunks per lane
+                                        (3, 512, 14337, -0.84), (7, 256, 14400, -0.84)])
 def test_exact_f32(exact_route, B, H, I, bias):
     inp = synth.make_ffn(B, H, I, gate_bias=bias, dtype=synth.F32, seed=[81, B, H, I])
     out, st, ref = check_ffn(inp)
@@ -101,7 +105,7 @@ def test_exact_whole_fp32_range(exact_route, entry, B):
     payload is all ones, and one above the largest bf16 (whose first part must
     not round to infinity).  Every token of the batch gives what it gives
     alone (the single-token kernels' fp32 products)."""
-    H, I, E = (4096, 4485, 1) if entry == "act" else (256, 520, 2)
+    H, I, E = (4096, 4485, 1) if entry == "act" else (256, 1040, 2)
     m = synth.make_moe(B, H, I, E, 1, gate_bias=-0.84, dtype=synth.BF16, seed=[85, B])
     x, wr, wg, wu, wd = (to_dev(a) for a in (m.x, m.w_router, m.w_gate, m.w_up, m.w_down_t))
     big = 3.4e38  # rounds to infinity in bf16
@@ -120,6 +124,7 @@ def test_exact_whole_fp32_range(exact_route, entry, B):
             return ts.ffn_sparse_act(v, wg[0], wu[0], wd[0], ts.TS_ACT_RELU_GATE, 0.1)
         return ts.moe_sparse(v, wr, wg, wu, wd, 1)[0]
 
+    assert launches(lambda: call(x), "batch_down") == 1
     got = call(x).cpu().numpy()
     want = np.concatenate([call(x[t:t + 1].contiguous()).cpu().numpy() for t in range(B)])
     assert np.isposinf(want[1]).all() or entry == "moe"

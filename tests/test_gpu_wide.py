@@ -11,6 +11,7 @@ import oracle
 from gpu_util import (TIGHT_SINGLE, assert_elementwise, check_ffn_output, compare_sets, ffn_inputs_to_dev, list_of,
                       moe_bound, rel_l2, to_dev)
 from paper_2406_05955_amd import synth
+from test_gpu_exact_batch import launches
 
 pytestmark = pytest.mark.gpu
 
@@ -50,12 +51,27 @@ def test_wide_ffn(B, H, I):
         assert compare_sets(list_of(st, "active_idx", t, "n_active"), (g > 0) & (u > 0), keep_a) == 0, t
 
 
-@pytest.mark.parametrize("B,H,I,E,K,skew", [(65, 512, 700, 8, 2, False), (128, 1032, 130, 4, 2, False),
-                                            (130, 256, 65, 8, 1, True), (256, 264, 300, 64, 4, False),
-                                            (100, 128, 33, 1, 1, False),
-                                            (66, 4096, 130, 4, 2, False), (70, 4104, 65, 2, 1, False)])
-def test_wide_moe(B, H, I, E, K, skew):
+@pytest.fixture
+def exact_route():
+    ts.tune_set("bx_exact", 1)  # small shapes as well
+    yield
+    ts.tune_set("bx_exact", 0)
+    ts.tune_set("down_chunks", 0)
+
+
+@pytest.mark.parametrize("B,H,I,E,K,skew,chunks,wide", [
+    (130, 520, 1205, 2, 2, False, 0, True), (200, 1032, 700, 4, 2, True, 0, True), (256, 264, 1300, 8, 4, True, 0, True),
+    # every workgroup starts at another fold of rows this long
+    (128, 4096, 700, 4, 2, False, 0, True), (130, 4104, 665, 2, 2, False, 0, True), (65, 3592, 640, 2, 2, False, 0, True),
+    (65, 8, 600, 2, 2, False, 0, True),
+    (130, 520, 2100, 2, 2, False, 1, True),  # a down chunk of 66 tiles
+    # whose plan does not fit the workspace: the single-token kernels
+    (65, 512, 700, 8, 2, False, 0, False), (128, 1032, 130, 4, 2, False, 0, False),
+    (130, 256, 65, 8, 1, True, 0, False), (256, 264, 300, 64, 4, False, 0, False), (100, 128, 33, 1, 1, False, 0, False),
+    (66, 4096, 130, 4, 2, False, 0, False), (70, 4104, 65, 2, 1, False, 0, False)])
+def test_wide_moe(exact_route, B, H, I, E, K, skew, chunks, wide):
     """skew: every token routed to expert 0, which then takes several groups."""
+    ts.tune_set("down_chunks", chunks)
     m = synth.make_moe(B, H, I, E, K, gate_bias=-0.84, dtype=synth.BF16, seed=[72, B, H, I, E, K])
     if skew:
         m.w_router[0, 0] = synth.f32_to_bf16_bits(np.float32([10.0]))[0]  # x[:, 0] = 1: a logit bias
@@ -67,6 +83,10 @@ def test_wide_moe(B, H, I, E, K, skew):
     ws.fill_(0xFF)
     dense = ts.moe_dense(*args, K, ws=ws)[0]
     torch.cuda.synchronize()
+    for call in (ts.moe_sparse, ts.moe_dense):
+        assert launches(lambda: call(*args, K, ws=ws), "batch_down") == (1 if wide else 0)
+    if skew:
+        assert (ref.topk_idx[:, 0] == 0).all()
     p = np.sort(ref.probs, axis=1)[:, ::-1]
     keep = [t for t in range(B) if K == E or abs(p[t, K - 1] - p[t, K]) > 1e-6 * p[t, K - 1]]
     assert idx.cpu().numpy()[keep].tolist() == ref.topk_idx[keep].tolist()

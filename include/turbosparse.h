@@ -157,8 +157,9 @@ typedef enum {
  * Other arguments as ts_ffn_sparse, same workspace size.  TS_ACT_RELU_GATE
  * with several tokens runs the batched kernels with x and Combined in three
  * bf16 parts (all 24 bits; TS_F32: fp32) where the matrices are large enough
- * for that to pay, otherwise the single-token kernels per token.  An unknown `act`, a non-finite tau, or a non-zero tau
- * with TS_ACT_DRELU returns TS_ERR_SHAPE.
+ * for that to pay, otherwise the single-token kernels per token.  An unknown
+ * `act`, a non-finite tau, or a non-zero tau with TS_ACT_DRELU returns
+ * TS_ERR_SHAPE.
  */
 ts_status ts_ffn_sparse_act(const float *x, const void *w_gate, const void *w_up, const void *w_down_t,
                             ts_dtype wdtype, int batch, int hidden, int inter, ts_act act, float tau,
@@ -224,8 +225,10 @@ size_t ts_moe_workspace_bytes(int batch, int hidden, int inter, int n_experts, i
  * its token's router; other batches run the matrix-core
  * path, each expert's tokens in groups of about twice the expected load (an
  * expert drawing more takes further groups and reads its weights once more
- * per group), above 64 tokens in groups of 64 with x and Combined in three
- * bf16 parts (all 24 bits).
+ * per group).  Above 64 tokens they do so, in groups of 64 with x and Combined
+ * in three bf16 parts (all 24 bits), where the weight readings saved pay for
+ * it and the groups fit the workspace (few tokens beside many experts do
+ * not); otherwise the single-token kernel runs per routed pair.
  */
 ts_status ts_moe_sparse(const float *x, const void *w_router, const void *w_gate, const void *w_up,
                         const void *w_down_t, ts_dtype wdtype, int batch, int hidden, int inter,

@@ -102,8 +102,8 @@ def _check(code: int, where: str):
 
 # A small call's time is the host's: per call at the 512 x 1792 layer, tensor
 # checks 2.2 us, the stream object 2.9, pointer objects 1.0, a workspace size
-# that the caller's own workspace makes needless 0.5, of 15.1 (the library's
-# two launches 8.2).  So pointers are passed as plain integers (the argument
+# that the caller's own workspace makes needless 0.5, of 14.0 (the library's
+# call with its two launches 6.5); now 10.8 (checks 1.6, stream 0.2).  So pointers are passed as plain integers (the argument
 # types convert them), the current stream is asked for as a handle where this
 # torch offers it, and well-formed tensors pass one combined test.
 def _ptr(t):

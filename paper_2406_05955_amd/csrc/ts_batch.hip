@@ -1439,9 +1439,10 @@ void launch_exact(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
 
 }  // namespace
 
-// One pass of the batched path for up to kBxMaxTokens tokens.  x and out are
-// offset to the pass's first token; topk / topw (MoE) are [batch][K] for the
-// pass's tokens.  Stats arrays are indexed from stats_base.
+// One pass of the batched path for the plan's tokens (up to kBxMaxTokens with
+// the two-part kernels of this file, up to kMaxBatch with the wide and the
+// fp32-exact ones).  x and out are offset to the pass's first token; topk /
+// topw (MoE) are [batch][K] for the pass's tokens.  Stats arrays are indexed from stats_base.
 ts_status run_batch(const float *x, const void *wg, const void *wu, const void *wd, size_t expert_stride,
                     const int32_t *topk, const float *topw, const BatchPlan &p, float *out,
                     const ts_ffn_stats *stats, int stats_base, void *ws, hipStream_t st, bool dense, bool xtok,

@@ -1,5 +1,6 @@
 // Device-side pieces shared by the batched kernels (ts_batch.hip: up to 64
-// token slots per weight set, ts_wide.hip: wide batches).
+// token slots per group, ts_rows.hip: a few fp32 tokens, ts_wide.hip: wide
+// batches).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -61,18 +62,19 @@ struct BxArgs {
     const float *topw;       // [B][K] routing weights, or null
     int32_t *gcount;         // [G]
     int32_t *tslot;          // [B][K][2] (group, slot) of each routed token
-    uint16_t *xhl;           // x fragments [G][hpad / 32][NX][64 lanes][8] bf16 (MFMA operand order)
+    uint16_t *xhl;           // x fragments [G][k-steps][NX][64 lanes][16 bytes] (MFMA operand order)
     int32_t *cnt;            // [G][ntiles][2] |union G|, |union A|
     uint8_t *arow;           // [G][ntiles][32] row within the tile of each active slot (slot 0's past |union A|)
-    uint16_t *hfrag;         // [G][ntiles][32 slots][2][bpad] Combined per active slot, bf16 high / low
+    uint16_t *hfrag;         // [G][ntiles][32 slots][P][bpad] Combined per active slot in P bf16 parts
+                             // (kBxF32: [32 slots][bpad] fp32)
     uint32_t *gmask;         // [G][ntiles][bpad] open-gate rows of the tile per token
     uint32_t *amask;         // [G][ntiles][bpad] active rows of the tile per token
     float *partial;          // [G][bpad][nchunks][H]
     float *out;              // [tokens][H]
     int want_masks;
     int dense;               // 1: every row is taken (the dense comparator)
-    const uint16_t *xtok;    // or null: every token's x as bf16 high / low parts, token-major (the MoE
-                             // router's split: per token xchunks chunks of 8 values, 32 bytes each)
+    const uint16_t *xtok;    // or null: every token's x in P bf16 parts, token-major (the MoE router's
+                             // split: per token xchunks chunks of 8 values, P 16-byte pieces each at xs_pos)
     int xchunks;
     int act;                 // activation (gate_threshold and the two functions beside it)
     float tau;

@@ -138,10 +138,12 @@ __device__ __forceinline__ uint32_t bf16_bits(float f) {
 }
 
 // Takes the next of P bf16 parts of v (returned) and leaves the rest in v.
-// Three parts stand in for products of the fp32 value itself, so they keep
-// its whole range: an infinity or a NaN is its first part alone (its rest
-// would be NaN), and a value above the largest bf16 takes that one instead of
-// rounding to infinity.  (Both are selects beside the rounding: they measure
+// Three parts stand in for products of the fp32 value itself, so they hold all
+// of v: an infinity or a NaN is its first part alone (its rest would be NaN),
+// and a value above the largest bf16 takes that one instead of rounding to
+// infinity.  This is about v only: an infinite weight meets the zero parts as
+// well, and inf * 0 is NaN where the fp32 product is infinite.  Below about
+// 1e-31 the lower parts are subnormal and lost (error 2.7e-5 at 1e-33).  (Both are selects beside the rounding: they measure
 // nothing in the kernels that split.)
 template <int P>
 __device__ __forceinline__ uint32_t bf16_take(float &v) {

@@ -141,12 +141,19 @@ struct BatchPlan {
 };
 
 // Wide batches: the workgroup-tiled kernels, for the FFN above kWdMinTokens
-// tokens (32 tokens 79 against 95 us per Mistral layer, 64 tokens 100
-// against 137, 256 tokens 197 against 527; at 16 the kernels of
-// ts_batch.hip read only the open W_up rows and are not bound by x) and for
-// the MoE layer above kBxMaxTokens.  A plan is taken only where it fits the
-// workspace that the shape's other plans need, so workspace sizes do not
-// depend on it.
+// tokens and for the MoE layer above kBxMaxTokens.  FFN, Mistral layer, us
+// against the kernels of ts_batch.hip, which read only the W_up rows that are
+// open for some token: 20% open gates, 17 tokens 91 / 99, 32 tokens 95 / 103,
+// 64 tokens 108 / 142, 256 tokens 190 / 529; 6%: 82 / 87, 88 / 96; 3%: 79 /
+// 78, 84 / 87; at 1%, which the host cannot know, reading every W_up row loses
+// up to 32 tokens: 76 / 69, 79 / 75 (40 tokens 81 / 102).  Smaller layers gain
+// at each.  At 16 tokens the others' x fits their registers.
+// A plan is taken only where it fits the workspace that the shape's other
+// plans need, so workspace sizes do not depend on it.  An FFN from hidden 512
+// and inter 1792 on always fits; a MoE layer has slots for every token in
+// every expert, and with few tokens beside its experts does not (4096 x 14336,
+// 16 experts, top 1, below 70 tokens; 64 experts, top 2, at any batch): such
+// calls stay on the single-token kernels.
 constexpr int kWdMinTokens = 16;
 constexpr int kRowsMaxTokens = 8;  // fp32 row streams (ts_rows.hip): tokens whose x fits LDS
 

@@ -221,6 +221,11 @@ __global__ __launch_bounds__(kRowThreads, 2) void bx_rows(BxArgs a, int nseg, in
 
 namespace {
 
+// Chunks per lane: a lane's chunks past its segment are loads of nothing, but
+// their products are issued, so rows of five or six chunks have forms of their
+// own (6 tokens, hidden 2052 25.4 us against 28.7 in the form of eight, 8
+// tokens 26.3 against 34.9; six chunks, hidden 3072, 8 tokens 29.8 against
+// 36.0); three or seven round up (a 64th to an 8th of the widest hidden).
 template <int T>
 void launch_rows_t(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     const int nch = p.hidden / 4;
@@ -238,6 +243,9 @@ void launch_rows_t(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
 
 }  // namespace
 
+// Tokens: the products of a slot past the batch are issued as well.  A form of
+// six serves 5 and 6 tokens (hidden 4096, 6 tokens 36.6 us against 40.5 in the
+// form of eight, 512 x 14000 15.6 against 18.4).
 void launch_rows(const BatchPlan &p, const BxArgs &a, hipStream_t st) {
     if (p.batch <= 4) launch_rows_t<4>(p, a, st);
     else if (p.batch <= 6) launch_rows_t<6>(p, a, st);

@@ -291,13 +291,16 @@ __global__ __launch_bounds__(kWdThreads, 2) void wd_gate_up(BxArgs a) {
     constexpr uint32_t XSTEP = GATHER ? KS * 4 * 16 * P : XCH * 16;  // bytes per stage
 
     u32x4 ra[D][NA], rb[D][NXL];
-    // MoE, rows of 8 KB and more: every workgroup starts at another fold of
-    // the hidden dimension.  In step, all would read the same 128-byte column
-    // of rows that far apart, and how many memory channels that meets depends
-    // on where the weights lie: Mixtral shape, 128 tokens, 402 to 475 us over
-    // several allocations, 398 to 400 with it.  Rows of 4 KB: 102 to 109 us
-    // without, 109 with.  The FFN (one weight set) gained nothing: 32 tokens
-    // 43.2 / 45.8 us, 256 tokens 102.4 / 104.9.
+    // MoE, rows above 6 KB (padded to 8 KB): every workgroup starts at another
+    // fold of the hidden dimension.  In step, all would read the same 128-byte
+    // column of rows that far apart, and how many memory channels that meets
+    // depends on where the weights lie.  8 experts, 128 tokens, over several
+    // allocations, without / with: 4096 x 14336 392 to 466 / 374 to 386 us,
+    // 4096 x 7168 204 to 237 / 192 to 194, 3584 x 7168 205 / 196, 8192 x 3584
+    // 199 to 212 / 186.  Shorter rows: 4 experts of 2048 x 7000 102 to 109 /
+    // 109, but 8 of 2048 x 7168 125 to 136 / 117 to 125 and 3072 x 7168 169 /
+    // 163; 1024 x 7168 the same.  The FFN (one weight set) gained nothing: 32
+    // tokens 43.2 / 45.8 us, 256 tokens 102.4 / 104.9.
     const int rot = GATHER && nst >= 64 ? 8 * ((int)(blockIdx.x / 8) % (nst / 8)) : 0;
     auto issue = [&](int d, int lst) {
         int st = lst;

@@ -324,35 +324,42 @@ bool plan_wide_moe(int batch, int hidden, int inter, int experts, int top_k, ts_
 
 // The single-token kernels read a weight set once per token (or routed
 // pair), the batched ones once: about one matrix's bytes per saved reading,
-// against two more launches and a longer chain (10 to 15 us).  What a saved
-// reading is worth depends on where it comes from: matrices below 32 MB stay
-// in the caches, and the second token of two streams beside the first.
-// Measured per layer, single-token time over batched (6 and 20% open gates),
-// at the bytes saved:
-//   fp32, matrices of 32 MB and more: 41 MB, 3 tokens (82 MB) 1.09 / 1.15;
-//     57 MB, 3 tokens (115) 1.37 / 1.33; 2 tokens: 82 MB 0.95, 117 MB 0.89 /
-//     0.91, 235 MB 1.30 / 1.25
-//   fp32, smaller: 4 MB, 32 tokens (115) 0.62 / 0.72; 14 MB, 8 (100) 0.66 /
-//     0.73; 20 MB, 12 (226) 0.95 / 1.04; 29 MB, 9 (230) 0.86 / 0.90; 10 MB,
-//     32 (316) 0.98 / 1.16; 20 MB, 16 (308) 1.27; 29 MB, 12 (316) 1.52
-//   bf16 (gate-only ReLU): 117 MB, 2 tokens (117) 0.75, 4 (352) 1.25; 20 MB,
-//     12 (226) 1.01 / 1.13, 17 (328) 0.99 / 1.15; 37 MB, 8 (258) 1.63 / 1.72
-//   MoE, fp32: 29 MB, 8 experts, 12 (118) 0.98, 4 experts, 8 (118) 0.77; 4 MB
-//     (170) 0.77, (207) 1.32; 41 MB, 8 experts, 12 (164) 0.89; 14 MB (286)
-//     1.31, (343) 1.29
-//   MoE, bf16 above 64 tokens: 1.8 MB, 2 experts, 65 (113) 0.56 / 0.66, 128
-//     (227) 0.96 / 1.17; 3.7 MB, 80 (289) 0.98 / 1.21; 3.7 MB, 128 (466) 1.23
+// against two more launches and a longer chain (10 to 20 us).  What a saved
+// reading costs them depends on where it comes from (matrices below 32 MB
+// stay in the caches, the second of two tokens streams beside the first) and
+// on whether all tokens' workgroups run at once: more than one per compute
+// unit take a second round.  The lines below are where some 190 fp32 FFN
+// shapes (2 to 32 tokens, hidden 512 to 4096, inter 1792 to 14336), 180 fp32
+// and 80 bf16 MoE shapes and 80 ReLU shapes, each measured by either route, are
+// best parted: on average 0.5 to 0.8% from always taking the faster one, the
+// worst choice 1.22 times it.  Per layer, single-token / batched us:
+//   fp32, matrices of 32 MB and more: 2 tokens 82 MB 41 / 42, 117 MB 46 / 50,
+//     235 MB 98 / 78; one round: 41 MB, 3 tokens (82 MB saved) 34 / 31 and 29 /
+//     31, 59 MB, 3 (117) 43 / 35; more: 59 MB, 6 (294) 63 / 40
+//   12 to 32 MB: one round: 14 MB, 8 (100) 21 / 30, 29 MB, 9 (230) 35 / 40;
+//     more: 20 MB, 8 (144) 34 / 31, 26 MB, 6 (131) 39 / 28, 29 MB, 5 (118) 30
+//     / 34
+//   smaller: 4 MB, 32 (115) 24 / 35, 7 MB, 32 (223) 36 / 40, 10 MB, 32 (316)
+//     43 / 41
+//   MoE, fp32: 29 MB, 4 experts, top 1, 8 tokens (118) 0.77, 12 (235) 1.22
+//     (times faster); 4 MB, 2 experts (170) 0.77, 8 experts (207) 1.32
+//   bf16, ReLU: 117 MB, 2 (117) 0.76, 4 (352) 1.25, 37 MB, 8 (258) 1.68; 20 MB,
+//     12 (226) 1.07.  MoE above 64 tokens: 2 MB, 2 experts, 65 (113) 0.61, 128
+//     (227) 1.07; 4 MB, 65 (231) 0.89, 80 (289) 1.10
 bool exact_pays(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt) {
     if (g_bx_exact.load() == 1) return batch > 1;
-    const long long saved = (long long)batch * top_k - experts;
-    const long long matrix = (long long)inter * hidden * esize(dt);
-    long long line = 288LL << 20;
-    if (experts == 1 && dt == TS_BF16) {
-        line = 240LL << 20;
-    } else if (experts == 1 && matrix >= 32LL << 20) {
-        line = (saved == 1 ? 192LL : 76LL) << 20;
+    const long long matrix = (long long)inter * hidden * esize(dt), MB = 1 << 20;
+    const long long slots = (long long)batch * top_k, saved = slots - experts;
+    if (saved <= 0) return false;
+    long long line = 240;
+    if (dt == TS_F32) {
+        const int tile = choose_pow2_tile(inter, (int)slots, kMaxPipeTile);
+        const bool one_round = slots * ((inter + tile - 1) / tile) <= kTargetTiles, large = matrix >= 32 * MB;
+        if (experts > 1) line = 180;
+        else if (saved == 1) line = 192;
+        else if (matrix >= 12 * MB) line = one_round ? (large ? 100 : 240) : (large ? 76 : 90);
     }
-    return saved > 0 && saved * matrix >= line;
+    return saved * matrix >= line * MB;
 }
 
 bool plan_exact(int batch, int hidden, int inter, int experts, int top_k, ts_dtype dt, size_t limit, BatchPlan *p) {

@@ -114,13 +114,15 @@ int main() {
     }
 
     // both sides of the size rule's lines: {batch, hidden, inter, experts, top_k, fp32, pays}
-    const int lines[][7] = {{3, 2048, 4097, 1, 1, 1, 0}, {3, 2048, 4900, 1, 1, 1, 1},     // fp32, 34 MB / 40 MB matrices
+    const int lines[][7] = {{3, 2048, 4097, 1, 1, 1, 0}, {3, 2048, 6500, 1, 1, 1, 1},     // fp32, 32 MB and more
                             {2, 4096, 12000, 1, 1, 1, 0}, {2, 4096, 12300, 1, 1, 1, 1},   // two tokens
-                            {10, 2048, 4000, 1, 1, 1, 0}, {11, 2048, 4000, 1, 1, 1, 1},   // below 32 MB
+                            {6, 1024, 5000, 1, 1, 1, 0}, {8, 1024, 5000, 1, 1, 1, 1},     // one round (240), two (320 workgroups)
+                            {9, 2048, 3500, 1, 1, 1, 0}, {10, 2048, 3500, 1, 1, 1, 1},    // (252, 280)
+                            {24, 512, 3500, 1, 1, 1, 0}, {40, 512, 3500, 1, 1, 1, 1},     // below 12 MB
                             {18, 2048, 3600, 1, 1, 0, 0}, {19, 2048, 3600, 1, 1, 0, 1},   // bf16
                             {65, 512, 1792, 2, 1, 0, 0}, {128, 512, 1792, 4, 2, 0, 1},    // MoE
-                            {12, 4096, 1792, 4, 1, 1, 0}, {16, 4096, 1792, 4, 1, 1, 1},
-                            {4, 4096, 14336, 8, 2, 0, 0}};                                // (no reading saved)
+                            {10, 4096, 1792, 4, 1, 1, 0}, {11, 4096, 1792, 4, 1, 1, 1},
+                            {4, 4096, 14336, 8, 2, 1, 0}, {4, 4096, 14336, 8, 2, 0, 0}};  // (no reading saved)
     for (const auto &l : lines)
         if (exact_pays(l[0], l[1], l[2], l[3], l[4], l[5] ? TS_F32 : TS_BF16) != (l[6] == 1))
             return fail("size rule", l[0], l[1], l[2], l[3]);

@@ -166,8 +166,12 @@ __device__ __forceinline__ int bx_swz(int r, int c) {
 
 // (k-steps and offsets in bytes of a row, Hb = its length.)  The fp32 and
 // three-part modes, whose other route is the single-token kernels' short fp32
-// chains, sum each batch from zero and add it to the accumulators (FOLD): a
-// chain of roundings spans one batch, not the wave's quarter.
+// chains, sum each batch from zero (FOLD) and add the sums of two batches of
+// two k-steps, or of one of four, to the accumulators: a chain of roundings
+// spans those, not the wave's quarter.  Error against theirs, 6% open gates,
+// fp32 12 / 24 tokens: hidden 512 1.00 / 1.00, 1024 0.88 / 0.87, 4096 0.65 / 0.65
+// (batches added one by one, a k-step's 16 products in one chain: 1.23 / 1.23,
+// 1.04 / 1.07, 0.76 / 0.86); ReLU 8 / 16 tokens, 2048: 0.67 / 0.68.
 template <int TOK, int MT, int KS, int D, bool GATHER = false, int M = kBxBf16x2>
 __device__ __forceinline__ void bx_kloop(const char *wbase, const uint32_t (&roff)[MT * KS], int Hb,
                                          const BxX<Bx<TOK, M>::NX> &xs, int ks0, int nbat, int lane, u32x4 *sw,
@@ -175,6 +179,7 @@ __device__ __forceinline__ void bx_kloop(const char *wbase, const uint32_t (&rof
     using S = Bx<TOK, M>;
     constexpr int NX = S::NX, NT = S::NT, CPR = 4 * KS, RPI = 16 / KS, NI = MT * KS;
     constexpr bool FOLD = M != kBxBf16x2;
+    static_assert(!FOLD || D == 2, "pairs of batches");
     static_assert(!GATHER || M == kBxBf16x2, "the router's split has two parts here");
     // each wave's k-steps (hpad / 128, hpad a multiple of kBxKQuant) come in
     // batches of KS; the ring below needs their count to be a multiple of D
@@ -182,6 +187,7 @@ __device__ __forceinline__ void bx_kloop(const char *wbase, const uint32_t (&rof
     const int lm = lane & 15, lq = lane >> 4;
     const int lc = lane % CPR, lr = lane / CPR;
     u32x4 w[D][NI], xv[D][NX][KS];
+    f32x4 pend[FOLD ? MT : 1][FOLD ? NT : 1];
     // weights: uniform base + 32-bit per-lane byte offset (row * Hb + k bytes)
     auto issue = [&](int d, int b) {
         const int kb = (ks0 + b * KS) * 64 + 16 * lc;
@@ -226,30 +232,26 @@ __device__ __forceinline__ void bx_kloop(const char *wbase, const uint32_t (&rof
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) part[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
             if constexpr (S::F32) {
-                // four chains of C k-steps' products (4 C each), added in pairs
-                auto chains = [&](auto cn) {
-                    constexpr int C = decltype(cn)::value;
+                // four chains of two k-steps' products (8 each), added in pairs (of
+                // one: 12 tokens of 2052 x 5003 31.5 -> 36.7 us)
 #pragma unroll
-                    for (int s = 0; s < KS; s += C)
+                for (int s = 0; s < KS; s += 2)
 #pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
+                    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                            for (int mt = 0; mt < MT; ++mt) {
-                                f32x4 p[4];
+                        for (int mt = 0; mt < MT; ++mt) {
+                            f32x4 p[4];
 #pragma unroll
-                                for (int j = 0; j < 4; ++j) p[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                            for (int j = 0; j < 4; ++j) p[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                                for (int h = 0; h < C; ++h)
+                            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                                    for (int j = 0; j < 4; ++j)
-                                        p[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                            __builtin_bit_cast(f32x4, av[mt][s + h])[j],
-                                            __builtin_bit_cast(f32x4, xv[d][nt][s + h])[j], p[j], 0, 0, 0);
-                                part[mt][nt] += (p[0] + p[1]) + (p[2] + p[3]);
-                            }
-                };
-                if (Hb < 4096) chains(std::integral_constant<int, 1>{});
-                else chains(std::integral_constant<int, 2>{});
+                                for (int j = 0; j < 4; ++j)
+                                    p[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                        __builtin_bit_cast(f32x4, av[mt][s + h])[j],
+                                        __builtin_bit_cast(f32x4, xv[d][nt][s + h])[j], p[j], 0, 0, 0);
+                            part[mt][nt] += (p[0] + p[1]) + (p[2] + p[3]);
+                        }
             } else {
                 // the lower parts' products first: what those round is small
 #pragma unroll
@@ -265,7 +267,11 @@ __device__ __forceinline__ void bx_kloop(const char *wbase, const uint32_t (&rof
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += part[mt][nt];
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (KS == 4) acc[mt][nt] += part[mt][nt];
+                    else if (d == 0) pend[mt][nt] = part[mt][nt];
+                    else acc[mt][nt] += pend[mt][nt] + part[mt][nt];
+                }
         } else {
 #pragma unroll
             for (int s = 0; s < KS; ++s)
@@ -370,8 +376,10 @@ __device__ __forceinline__ void bx_token_masks(const bool (&pred)[2][NT][4], con
     }
 }
 
+// (fp32: three workgroups per unit hold 168 registers; with 190 to 205 two, and
+// a grid of several rounds, an MoE layer of 4 experts of 592 x 6000, 34 -> 42 us)
 template <int TOK, int KS, int D, bool GATHER = false, int M = kBxBf16x2>
-__global__ __launch_bounds__(256, TOK >= 64 ? 1 : 2) void bx_gate_up(BxArgs a) {
+__global__ __launch_bounds__(256, TOK >= 64 ? 1 : (M == kBxF32 ? 3 : 2)) void bx_gate_up(BxArgs a) {
     using S = Bx<TOK, M>;
     constexpr int NT = S::NT, NX = S::NX;
     constexpr int CPR = 4 * KS, RPI = 16 / KS;

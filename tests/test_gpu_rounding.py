@@ -5,10 +5,14 @@ shape makes one chain of roundings the long one: the gate and up sums over
 the hidden dimension, the down sums over a chunk's rows, the sums over the
 chunks.
 
-Bounds: the errors' norms are those of some thousands of independent
-roundings (tokens x active neurons), so either scatters by 1 to 2% of itself;
-3% between exact routes.  With two bf16 parts the same split rounds both
-results, so what differs is the sums alone: 0.5%."""
+Bounds: the error's norm is that of some thousands of independent roundings
+(tokens x active neurons), the large Combined values weighing most: of one
+draw's two errors, their ratio scatters by some 4% (30 draws at hidden 512
+gave a mean of 1.00), over 6 draws by under 2%; so 6 draws and 3% between
+exact routes.  With two bf16 parts the same split rounds both results, so
+what differs is the sums alone: 0.5%, one draw.  The chains that this guards
+against measured 1.02 to 1.06 (two parts) and 1.07 to 2.3.
+"""
 import pytest
 import torch
 
@@ -53,34 +57,37 @@ def exact(m, args, act, tau):
     ("ffn", synth.F32, 6, 512, 26000, 1, 1, 0.0, {"down_chunks": 400}, 1.03),  # the sums over the chunks
 ])
 def test_no_more_rounding(entry, dtype, B, H, I, E, K, bias, tune, bound):
-    m = synth.make_moe(B, H, I, E, K, gate_bias=bias, dtype=dtype, seed=[91, B, H, I])
-    args = tuple(to_dev(a) for a in (m.x, m.w_router, m.w_gate, m.w_up, m.w_down_t))
-    x, wr, wg, wu, wd = args
     tau = 0.25 if entry == "act" else 0.0
-
-    def call():
-        if entry == "ffn":
-            return ts.ffn_sparse(x, wg[0], wu[0], wd[0])
-        if entry == "act":
-            return ts.ffn_sparse_act(x, wg[0], wu[0], wd[0], ts.TS_ACT_RELU_GATE, tau)
-        return ts.moe_sparse(x, wr, wg, wu, wd, K)[0]
-
-    ref = exact(m, args, entry == "act", tau)
     knob = "bx_wide" if dtype == synth.BF16 and entry == "ffn" else "batch_path"
-    try:
-        for k, v in tune.items():
-            ts.tune_set(k, v)
-        got = call()
-        assert launches(call, "batch_down") == 1  # (the route under test)
-        for k in tune:
-            ts.tune_set(k, 0)
-        ts.tune_set(knob, 1)
-        old = call()
-        torch.cuda.synchronize()
-    finally:
-        ts.tune_set(knob, 0)
-        for k in tune:
-            ts.tune_set(k, 0)
-    e_new, e_old = ((o.double() - ref).norm().item() / ref.norm().item() for o in (got, old))
-    print(f"error {e_new:.3e}, before {e_old:.3e}, ratio {e_new / e_old:.4f}")
-    assert 0 < e_new <= bound * e_old
+    sq_new = sq_old = 0.0
+    for draw in range(1 if bound < 1.01 else 6):
+        m = synth.make_moe(B, H, I, E, K, gate_bias=bias, dtype=dtype, seed=[91, B, H, I, draw])
+        args = tuple(to_dev(a) for a in (m.x, m.w_router, m.w_gate, m.w_up, m.w_down_t))
+        x, wr, wg, wu, wd = args
+
+        def call():
+            if entry == "ffn":
+                return ts.ffn_sparse(x, wg[0], wu[0], wd[0])
+            if entry == "act":
+                return ts.ffn_sparse_act(x, wg[0], wu[0], wd[0], ts.TS_ACT_RELU_GATE, tau)
+            return ts.moe_sparse(x, wr, wg, wu, wd, K)[0]
+
+        ref = exact(m, args, entry == "act", tau)
+        try:
+            for k, v in tune.items():
+                ts.tune_set(k, v)
+            got = call()
+            assert launches(call, "batch_down") == 1  # (the route under test)
+            for k in tune:
+                ts.tune_set(k, 0)
+            ts.tune_set(knob, 1)
+            old = call()
+            torch.cuda.synchronize()
+        finally:
+            ts.tune_set(knob, 0)
+            for k in tune:
+                ts.tune_set(k, 0)
+        sq_new, sq_old = (q + ((o.double() - ref).norm().item() / ref.norm().item()) ** 2
+                          for q, o in ((sq_new, got), (sq_old, old)))
+    print(f"error ratio {(sq_new / sq_old) ** 0.5:.4f}")
+    assert 0 < sq_new <= bound ** 2 * sq_old
